@@ -1,15 +1,16 @@
-// Kernel selection: the bf16 fast kernels where they cover the shape, the
-// generic kernels otherwise (and for the fp32 validation mode).
+// Kernel selection: the bf16 (fp32) matrix-core kernels where they cover the
+// shape; otherwise the strided GEMM, and the fp32 matrix-core attention.
 #include "tp_common.hpp"
 #include "tp_kernels.hpp"
 
 namespace tp {
 
-hipError_t attn_fwd_generic(int dtype, const AttnArgs& a, hipStream_t s);
-hipError_t attn_bwd_generic(int dtype, const AttnArgs& a, hipStream_t s);
+hipError_t attn_fwd_f32(int dtype, const AttnArgs& a, hipStream_t s);
+hipError_t attn_bwd_f32(int dtype, const AttnArgs& a, hipStream_t s);
 
 hipError_t gemm_mfma_bf16(const GemmArgs& a, hipStream_t s);
 hipError_t gemm_dma_bf16(const GemmArgs& a, hipStream_t s);
+hipError_t gemm_f32(const GemmArgs& a, hipStream_t s);
 
 hipError_t gemm(int dtype, const GemmArgs& a, hipStream_t s) {
   clear_stale_error();
@@ -17,6 +18,9 @@ hipError_t gemm(int dtype, const GemmArgs& a, hipStream_t s) {
     hipError_t e = gemm_dma_bf16(a, s);
     if (e != hipErrorNotSupported) return e;
     e = gemm_mfma_bf16(a, s);
+    if (e != hipErrorNotSupported) return e;
+  } else {
+    const hipError_t e = gemm_f32(a, s);
     if (e != hipErrorNotSupported) return e;
   }
   // fp16 operands have no generic kernel (the stage only asks for them where
@@ -35,7 +39,7 @@ hipError_t attn_fwd(int dtype, const AttnArgs& a, hipStream_t s) {
     if (e != hipErrorNotSupported) return e;
   }
   if (a.f16) return hipErrorNotSupported;
-  return attn_fwd_generic(dtype, a, s);
+  return attn_fwd_f32(dtype, a, s);
 }
 
 hipError_t attn_bwd(int dtype, const AttnArgs& a, hipStream_t s) {
@@ -45,7 +49,7 @@ hipError_t attn_bwd(int dtype, const AttnArgs& a, hipStream_t s) {
     if (e != hipErrorNotSupported) return e;
   }
   if (a.f16) return hipErrorNotSupported;
-  return attn_bwd_generic(dtype, a, s);
+  return attn_bwd_f32(dtype, a, s);
 }
 
 }  // namespace tp

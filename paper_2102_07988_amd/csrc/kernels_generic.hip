@@ -1,8 +1,6 @@
-// Generic kernels of the stage: a strided tiled-FMA GEMM with the fused
-// epilogues, straightforward prefix-causal attention forward/backward (one
-// block per (query, head)), LayerNorm forward/backward, column reductions.
-// These carry the fp32 validation mode and every shape the bf16 fast kernels
-// do not take.
+// Generic kernels of the stage: a strided tiled-FMA GEMM with the fused epilogues
+// for the operands the matrix-core GEMMs do not take (unaligned parameters),
+// LayerNorm forward/backward, column reductions.
 #include "tp_common.hpp"
 #include "tp_epilogue.hpp"
 #include "tp_kernels.hpp"
@@ -88,119 +86,6 @@ static hipError_t gemm_generic_t(const GemmArgs& a, hipStream_t s) {
 
 hipError_t gemm_generic(int dtype, const GemmArgs& a, hipStream_t s) {
   return dtype == DT_FP32 ? gemm_generic_t<float>(a, s) : gemm_generic_t<bf16>(a, s);
-}
-
-// ------------------------------------------------------- generic attention
-
-// One block per (query row, head).  LDS: scores [Lmax] (+ dP [Lmax] for bwd),
-// q and dO rows, reduction scratch.
-template <typename T>
-__global__ __launch_bounds__(256) void attn_fwd_generic_kernel(AttnArgs a0) {
-  extern __shared__ float sm[];
-  const AttnArgs a = attn_seq_view<T>(a0);
-  const int i = blockIdx.x, t = a.l + i, h = blockIdx.y, d = a.d, H = a.ld;  // H: row stride
-  float* S = sm;
-  float* qs = sm + a.Lmax;
-  float* red = qs + 128;
-  const T* q = (const T*)a.q + (long)i * H + h * d;
-  for (int j = threadIdx.x; j < d; j += blockDim.x) qs[j] = ld(q + j);
-  __syncthreads();
-  float mx = -INFINITY;
-  for (int s = threadIdx.x; s <= t; s += blockDim.x) {
-    const T* k = (const T*)a.kc + (long)s * H + h * d;
-    float dot = 0.f;
-    for (int j = 0; j < d; ++j) dot += qs[j] * ld(k + j);
-    dot *= a.scale;
-    S[s] = dot;
-    mx = fmaxf(mx, dot);
-  }
-  mx = block_max(mx, red);
-  float sum = 0.f;
-  for (int s = threadIdx.x; s <= t; s += blockDim.x) {
-    const float e = __expf(S[s] - mx);
-    S[s] = e;
-    sum += e;
-  }
-  sum = block_sum(sum, red);
-  const float inv = 1.f / sum;
-  for (int j = threadIdx.x; j < d; j += blockDim.x) {
-    float acc = 0.f;
-    for (int s = 0; s <= t; ++s) acc += S[s] * ld((const T*)a.vc + (long)s * H + h * d + j);
-    st((T*)a.o + (long)i * H + h * d + j, acc * inv);
-  }
-  if (threadIdx.x == 0) a.lse[(long)h * a.Lmax + t] = mx + logf(sum);
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void attn_bwd_generic_kernel(AttnArgs a0) {
-  extern __shared__ float sm[];
-  const AttnArgs a = attn_seq_view<T>(a0);
-  const int i = blockIdx.x, t = a.l + i, h = blockIdx.y, d = a.d, H = a.ld;  // H: row stride
-  float* P = sm;
-  float* dS = sm + a.Lmax;
-  float* qs = dS + a.Lmax;
-  float* ds_ = qs + 128;
-  float* red = ds_ + 128;
-  for (int j = threadIdx.x; j < d; j += blockDim.x) {
-    qs[j] = ld((const T*)a.q + (long)i * H + h * d + j);
-    ds_[j] = ld((const T*)a.dout + (long)i * H + h * d + j);
-  }
-  __syncthreads();
-  const float lse = a.lse[(long)h * a.Lmax + t];
-  float Dp = 0.f;
-  for (int s = threadIdx.x; s <= t; s += blockDim.x) {
-    const T* k = (const T*)a.kc + (long)s * H + h * d;
-    const T* v = (const T*)a.vc + (long)s * H + h * d;
-    float dot = 0.f, dpv = 0.f;
-    for (int j = 0; j < d; ++j) {
-      dot += qs[j] * ld(k + j);
-      dpv += ds_[j] * ld(v + j);
-    }
-    const float p = __expf(dot * a.scale - lse);
-    P[s] = p;
-    dS[s] = dpv;
-    Dp += p * dpv;
-  }
-  const float D = block_sum(Dp, red);
-  for (int s = threadIdx.x; s <= t; s += blockDim.x) dS[s] = P[s] * (dS[s] - D);
-  __syncthreads();
-  for (int j = threadIdx.x; j < d; j += blockDim.x) {
-    float acc = 0.f;
-    for (int s = 0; s <= t; ++s) acc += dS[s] * ld((const T*)a.kc + (long)s * H + h * d + j);
-    st((T*)a.dq + (long)i * a.ld_dq + h * d + j, acc * a.scale);
-  }
-  const long tot = (long)(t + 1) * d;
-  for (long e = threadIdx.x; e < tot; e += blockDim.x) {
-    const int s = (int)(e / d), j = (int)(e % d);
-    atomicAdd(a.dk + (long)s * H + h * d + j, dS[s] * qs[j] * a.scale);
-    atomicAdd(a.dv + (long)s * H + h * d + j, P[s] * ds_[j]);
-  }
-}
-
-template <typename T>
-static hipError_t attn_generic_t(const AttnArgs& a, bool bwd, hipStream_t s) {
-  if (a.need) return hipSuccess;  // no scratch
-  const size_t lds = bwd ? (2 * (size_t)a.Lmax + 256 + 16) * 4 : ((size_t)a.Lmax + 128 + 16) * 4;
-  if (lds > 160 * 1024) return hipErrorInvalidValue;
-  if (lds > 64 * 1024) {
-    const void* fn = bwd ? (const void*)attn_bwd_generic_kernel<T>
-                         : (const void*)attn_fwd_generic_kernel<T>;
-    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
-  dim3 grid(a.r - a.l, a.heads, a.bs);
-  if (bwd)
-    attn_bwd_generic_kernel<T><<<grid, 256, lds, s>>>(a);
-  else
-    attn_fwd_generic_kernel<T><<<grid, 256, lds, s>>>(a);
-  return hipGetLastError();
-}
-
-hipError_t attn_fwd_generic(int dtype, const AttnArgs& a, hipStream_t s) {
-  return dtype == DT_FP32 ? attn_generic_t<float>(a, false, s) : attn_generic_t<bf16>(a, false, s);
-}
-hipError_t attn_bwd_generic(int dtype, const AttnArgs& a, hipStream_t s) {
-  return dtype == DT_FP32 ? attn_generic_t<float>(a, true, s) : attn_generic_t<bf16>(a, true, s);
 }
 
 // ------------------------------------------------------------- LayerNorm

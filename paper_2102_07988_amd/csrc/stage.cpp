@@ -139,7 +139,7 @@ bool config_supported(const tp_stage_config* c) {
   const int d = c->hidden / c->heads;
   if (d != 16 && d != 32 && d != 64 && d != 128) return false;
   if (c->hidden % 8 || c->hidden > 16384) return false;  // LayerNorm rows live in registers
-  // the generic attention keeps one score row per block in LDS
+  // longest sequence the stage accepts (20344 tokens)
   if ((2 * (size_t)c->max_seq + 272) * 4 > 160 * 1024) return false;
   return true;
 }

@@ -104,11 +104,6 @@ __device__ inline float wave_sum(float v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
 }
-__device__ inline float wave_max(float v) {
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
-
 // Block-wide sum for blockDim.x a multiple of 64 (<= 1024).  `red` is LDS of
 // >= 16 floats.  Every thread gets the result.
 __device__ inline float block_sum(float v, float* red) {
@@ -119,16 +114,6 @@ __device__ inline float block_sum(float v, float* red) {
   __syncthreads();
   float s = 0.f;
   for (int i = 0; i < nw; ++i) s += red[i];
-  return s;
-}
-__device__ inline float block_max(float v, float* red) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  v = wave_max(v);
-  __syncthreads();
-  if (lane == 0) red[w] = v;
-  __syncthreads();
-  float s = -INFINITY;
-  for (int i = 0; i < nw; ++i) s = fmaxf(s, red[i]);
   return s;
 }
 
