@@ -56,10 +56,13 @@ __device__ inline int swz_kc(int r) {
 // 4 (k mod 4) (64-byte steps); rows of 384 bytes (R = 192) already alternate
 // between bank 0 and bank 32, so XOR 4 on rows 2 and 3 of each 4 suffices and
 // keeps the 24 chunks of a row within range.
+// Rows of 128 bytes (R = 64) alternate between bank 0 and bank 32 too and take the
+// same XOR; the 4 rows of a read of 64-byte rows (R = 32) are contiguous.
 template <int R>
 __device__ inline int swz_mc(int k) {
-  static_assert(R % 128 == 0 || R == 192, "transposing-read swizzle needs R = 128 j or 192");
-  if constexpr (R == 192) return ((k >> 1) & 1) << 2;
+  static_assert(R % 128 == 0 || R == 192 || R == 64 || R == 32, "no transposing-read swizzle");
+  if constexpr (R == 32) return 0;
+  else if constexpr (R == 192 || R == 64) return ((k >> 1) & 1) << 2;
   else return (k & 3) << 2;
 }
 
@@ -100,6 +103,35 @@ struct DmaPlan {
         const int gc = min(r0 + logical * 8, rmax - 8);
         off[i] = (uint32_t)(((long)krow * ld + gc) * 2);
       }
+    }
+  }
+  // The last k-tile of a reduction that is not whole k-tiles (kvalid < BK values,
+  // a multiple of 8 for KC): chunks past it repeat the last valid one, so every
+  // address stays inside the operand; zero_tail clears them once they landed.
+  __device__ static void issue_tail(const uint16_t* origin, long ld, int r0, int rmax, int kvalid,
+                                    uint16_t* lds, int w, int lane) {
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+      const int s = i * NTH + w * 64 + lane;
+      long o;
+      if constexpr (KC) {
+        constexpr int CPR = BK / 8;
+        const int row = s / CPR, logical = (s % CPR) ^ swz_kc<BK>(row);
+        o = (long)min(r0 + row, rmax - 1) * ld + min(logical * 8, kvalid - 8);
+      } else {
+        constexpr int CPR = R / 8;
+        const int krow = s / CPR, logical = (s % CPR) ^ swz_mc<R>(krow);
+        o = (long)min(krow, kvalid - 1) * ld + min(r0 + logical * 8, rmax - 8);
+      }
+      dma16(origin + o, lds + (i * NTH + w * 64) * 8);
+    }
+  }
+  __device__ static void zero_tail(int kvalid, uint16_t* lds) {
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+      const int s = i * NTH + threadIdx.x;
+      const int k = KC ? ((s % (BK / 8)) ^ swz_kc<BK>(s / (BK / 8))) * 8 : s / (R / 8);
+      if (k >= kvalid) *(uint4*)(lds + s * 8) = make_uint4(0, 0, 0, 0);
     }
   }
   // origin: X + k0 (KC) or X + k0 * ld (MC), wave-uniform; w: wave index (uniform)
@@ -198,9 +230,10 @@ struct TileWalk {
 // operand (the weights of a slice-shaped product, streamed from HBM) one
 // k-tile further ahead than A (activations, L2-resident).
 // F16: both operands are fp16 (the mixed-precision query/key/value product),
-// otherwise bf16.
+// otherwise bf16.  TAIL: K need not be whole k-tiles; the values of the last tile
+// past K are zeroed in LDS, in both operands, between two barriers.
 template <int BM, int BN, int BK, int WGM, int WGN, bool A_KC, bool B_KC, int EPI, bool SPLIT,
-          int STAGES, int SB, bool F16>
+          int STAGES, int SB, bool F16, bool TAIL>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_dma_kernel(GemmArgs a) {
   constexpr int NTH = 64 * WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN, FM = WM / 32, FN = WN / 32;
@@ -214,6 +247,12 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_dma_kernel(GemmArgs a) {
   static_assert(SB == STAGES || (STAGES == 2 && SB == 3), "unsupported ring shape");
   static_assert((BK / 16) % 2 == 0, "fragment buffers alternate per k-step across k-tiles");
   constexpr int LPT_B = BK * BN / 8 / NTH;
+  // the epilogue's wave patches take the ring stage no wave reads in the last
+  // k-tile; with separate rings, or where they are larger than a stage, the LDS
+  // base once every wave has left the loop
+  constexpr int PATCH = WGM * WGN * 32 * 36 * 2;  // elements
+  constexpr bool PATCH_AT_BASE = BLEAD || PATCH > STAGE;
+  static_assert(PATCH <= (BLEAD ? STAGES * TILE_A : STAGES * STAGE), "epilogue patch exceeds LDS");
   extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
 
   const uint16_t* A = (const uint16_t*)a.A;
@@ -224,7 +263,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_dma_kernel(GemmArgs a) {
   const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;
   const int kbeg = SPLIT ? blockIdx.z * a.k_split : 0;
   const int kend = SPLIT ? min(a.K, kbeg + a.k_split) : a.K;
-  const int nk = (kend - kbeg) / BK;
+  const int nk = TAIL ? (kend - kbeg + BK - 1) / BK : (kend - kbeg) / BK;
+  const int kvalid = kend - kbeg - (nk - 1) * BK;  // TAIL: values of the last k-tile
   const uint32_t sbase = lds_addr(smem);
 
   int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
@@ -243,13 +283,19 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_dma_kernel(GemmArgs a) {
   auto issue_a = [&](int kt) {
     uint16_t* st = smem + (kt % STAGES) * (BLEAD ? TILE_A : STAGE);
     const long k = kbeg + kt * BK;
-    plan_a.issue(A + (A_KC ? k : k * lda), st, wu);
+    if (TAIL && kt == nk - 1 && kvalid < BK)
+      plan_a.issue_tail(A + (A_KC ? k : k * lda), lda, m0, a.M, kvalid, st, wu, lane);
+    else
+      plan_a.issue(A + (A_KC ? k : k * lda), st, wu);
   };
   auto issue_b = [&](int kt) {
     uint16_t* st = BLEAD ? smem + STAGES * TILE_A + (kt % SB) * TILE_B
                          : smem + (kt % STAGES) * STAGE + TILE_A;
     const long k = kbeg + kt * BK;
-    plan_b.issue(B + (B_KC ? k : k * ldb), st, wu);
+    if (TAIL && kt == nk - 1 && kvalid < BK)
+      plan_b.issue_tail(B + (B_KC ? k : k * ldb), ldb, n0, a.N, kvalid, st, wu, lane);
+    else
+      plan_b.issue(B + (B_KC ? k : k * ldb), st, wu);
   };
   // DMA of the k-tiles that iteration kt brings in (their stages were last read
   // in iteration kt - 1, before its closing barrier)
@@ -297,6 +343,16 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_dma_kernel(GemmArgs a) {
       wait_tiles<LPT, STAGES - 2>(min(STAGES - 2, nk - 1 - j));
     }
     __builtin_amdgcn_s_barrier();
+    if constexpr (TAIL) {
+      static_assert(!BLEAD, "the tail is cleared in single-ring kernels only");
+      if (j == nk - 1 && kvalid < BK) {
+        uint16_t* st = smem + (j % STAGES) * STAGE;
+        plan_a.zero_tail(kvalid, st);
+        plan_b.zero_tail(kvalid, st + TILE_A);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+      }
+    }
   };
   auto tile_a = [&](int j) { return sbase + (j % STAGES) * (BLEAD ? TILE_A : STAGE) * 2; };
   auto tile_b = [&](int j) {
@@ -409,12 +465,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_dma_kernel(GemmArgs a) {
 
   if constexpr (SPLIT || EPI == EPI_ACC_F32) {
     // fp32 outputs: each 32 x 32 sub-tile goes through a wave-private LDS patch
-    // (in the ring stage no wave reads in the last iteration, or, with separate
-    // rings, at the LDS base once every wave has left the loop)
-    static_assert(WGM * WGN * 32 * 36 * 4 <= (BLEAD ? STAGES * TILE_A : STAGE) * 2,
-                  "epilogue patch exceeds its region");
-    if constexpr (BLEAD) __builtin_amdgcn_s_barrier();
-    float* patch = (float*)(smem + (BLEAD ? 0 : (nk % STAGES) * STAGE)) + wave * (32 * 36);
+    if constexpr (PATCH_AT_BASE) __builtin_amdgcn_s_barrier();
+    float* patch = (float*)(smem + (PATCH_AT_BASE ? 0 : (nk % STAGES) * STAGE)) + wave * (32 * 36);
     float* out = SPLIT ? a.ws + (long)blockIdx.z * a.M * a.N : (float*)a.C;
     const long ldo = SPLIT ? a.N : a.ldc;
     // sub-tile rows leave as whole 128-byte lines: in step q (0..3) lane l
@@ -486,8 +538,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_dma_kernel(GemmArgs a) {
     // as 8-column row segments (in step q of 2, lane l takes row 16q + l/4,
     // columns 8 (l%4) .. +7), one 16-byte access per operand; N % 8 == 0, so a
     // segment is either inside the output or past its edge
-    if constexpr (BLEAD) __builtin_amdgcn_s_barrier();
-    float* patch = (float*)(smem + (BLEAD ? 0 : (nk % STAGES) * STAGE)) + wave * (32 * 36);
+    if constexpr (PATCH_AT_BASE) __builtin_amdgcn_s_barrier();
+    float* patch = (float*)(smem + (PATCH_AT_BASE ? 0 : (nk % STAGES) * STAGE)) + wave * (32 * 36);
     const int er = lane >> 2, ec = (lane & 3) * 8;
 #pragma unroll
     for (int i = 0; i < FM; ++i)
@@ -510,7 +562,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_dma_kernel(GemmArgs a) {
 }
 
 template <int BM, int BN, int BK, int WGM, int WGN, bool A_KC, bool B_KC, int STAGES, int SB,
-          bool SPLIT, bool F16>
+          bool SPLIT, bool F16, bool TAIL>
 hipError_t launch_dma(const GemmArgs& a, hipStream_t s) {
   constexpr int NTH = 64 * WGM * WGN;
   constexpr size_t lds = ((size_t)STAGES * BM + (size_t)SB * BN) * BK * 2;
@@ -527,7 +579,7 @@ hipError_t launch_dma(const GemmArgs& a, hipStream_t s) {
   if (hipGetDevice(&dev) != hipSuccess) dev = 32;
 #define TP_LAUNCH(E)                                                                         \
   do {                                                                                       \
-    auto* fn = gemm_dma_kernel<BM, BN, BK, WGM, WGN, A_KC, B_KC, E, SPLIT, STAGES, SB, F16>;\
+    auto* fn = gemm_dma_kernel<BM, BN, BK, WGM, WGN, A_KC, B_KC, E, SPLIT, STAGES, SB, F16, TAIL>; \
     static std::atomic<uint32_t> attr_set{0};                                                \
     const uint32_t bit = dev < 32 ? 1u << dev : 0u;                                          \
     if (!bit || !(attr_set.load(std::memory_order_acquire) & bit)) {                         \
@@ -546,20 +598,22 @@ hipError_t launch_dma(const GemmArgs& a, hipStream_t s) {
     TP_LAUNCH(EPI_QKV);
   } else if constexpr (!A_KC && !B_KC) {
     // m/n-contiguous operands on both sides: the weight-gradient products
+    if (a.epi != EPI_ACC_F32) return hipErrorNotSupported;
+    TP_LAUNCH(EPI_ACC_F32);
+  } else if constexpr (B_KC) {
+    // the forward's products
     switch (a.epi) {
-      case EPI_STORE: TP_LAUNCH(EPI_STORE); break;
-      case EPI_ACC_F32: TP_LAUNCH(EPI_ACC_F32); break;
-      default: return hipErrorNotSupported;
-    }
-  } else {
-    switch (a.epi) {
-      case EPI_STORE: TP_LAUNCH(EPI_STORE); break;
       case EPI_QKV: TP_LAUNCH(EPI_QKV); break;
       case EPI_RESID: TP_LAUNCH(EPI_RESID); break;
       case EPI_GELU: TP_LAUNCH(EPI_GELU); break;
+      default: return hipErrorNotSupported;
+    }
+  } else {
+    // the backward's products with a weight matrix
+    switch (a.epi) {
+      case EPI_STORE: TP_LAUNCH(EPI_STORE); break;
       case EPI_DGELU: TP_LAUNCH(EPI_DGELU); break;
-      case EPI_ACC_F32: TP_LAUNCH(EPI_ACC_F32); break;
-      default: return hipErrorInvalidValue;
+      default: return hipErrorNotSupported;
     }
   }
 #undef TP_LAUNCH
@@ -567,141 +621,222 @@ hipError_t launch_dma(const GemmArgs& a, hipStream_t s) {
 }
 
 
-// One DMA GEMM launch.  Every configuration holds one workgroup per CU (its
-// LDS ring takes most of the 160 KB), so when the tile count is low the
-// reduction is split (whole k-tiles, the last split may be shorter).
-// force_splits > 0 takes that many splits (at most; as k-tiles allow),
-// otherwise the split count comes from the cost model below (<= 8 splits of
-// >= 8 k-tiles).  With splits2 > 0 and 0 < cols1 < the column-tile count, the
-// product runs as two split launches: column tiles [0, cols1) with
-// force_splits splits, the rest with splits2 (when the partials fit), and one
-// reduction over both.
-template <int BM, int BN, int BK, int WGM, int WGN, bool A_KC, bool B_KC, int STAGES,
-          int SB, bool F16>
-hipError_t run_dma(GemmArgs a, hipStream_t s, int force_splits = 0, int splits2 = 0,
-                   int cols1 = 0) {
+// One DMA GEMM product with the given number of splits over the reduction (whole
+// k-tiles, the last split may be shorter), 1 = no partial sums.  With splits2 > 0
+// and 0 < cols1 < the column-tile count, the product runs as two split launches:
+// column tiles [0, cols1) with `splits`, the rest with splits2, and one reduction
+// over both.  The caller has checked that the partials fit the workspace.
+template <int BM, int BN, int BK, int WGM, int WGN, bool A_KC, bool B_KC, int STAGES, int SB,
+          bool F16, bool TAIL>
+hipError_t run_dma(GemmArgs a, hipStream_t s, int splits, int splits2, int cols1) {
   constexpr int CUS = 256;
-  if (a.K % BK) return hipErrorNotSupported;
   const long tiles = (long)cdiv(a.M, BM) * cdiv(a.N, BN);
-  const int nkt = a.K / BK;
-  if (force_splits > 0 && splits2 > 0 && cols1 > 0 && (long)cols1 * BN < a.N && a.ws) {
+  const int nkt = cdiv(a.K, BK);
+  if (splits2 > 0 && cols1 > 0 && (long)cols1 * BN < a.N) {
     const int n1 = cols1 * BN, n2 = a.N - n1;
-    const int ks1 = cdiv(nkt, std::min(force_splits, nkt)) * BK;
-    const int ks2 = cdiv(nkt, std::min(splits2, nkt)) * BK;
+    const int ks1 = cdiv(nkt, splits) * BK, ks2 = cdiv(nkt, splits2) * BK;
     const int s1 = cdiv(a.K, ks1), s2 = cdiv(a.K, ks2);
-    const long p1 = (long)s1 * a.M * n1, need = p1 + (long)s2 * a.M * n2;
-    if (need <= a.ws_elems) {
-      if (a.need) {
-        *a.need = need;
-        return hipSuccess;
-      }
-      GemmArgs g = a;
-      g.N = n1, g.k_split = ks1, g.splits = s1;
-      hipError_t e = launch_dma<BM, BN, BK, WGM, WGN, A_KC, B_KC, STAGES, SB, true, F16>(g, s);
-      if (e != hipSuccess) return e;
-      g = a;
-      g.N = n2, g.k_split = ks2, g.splits = s2;
-      g.B = (const uint16_t*)a.B + (long)n1 * a.sbn;
-      g.ws = a.ws + p1, g.ws_elems = a.ws_elems - p1;
-      e = launch_dma<BM, BN, BK, WGM, WGN, A_KC, B_KC, STAGES, SB, true, F16>(g, s);
-      if (e != hipSuccess) return e;
-      GemmArgs r = a;
-      r.splits = s1, r.splits2 = s2, r.split_cols = n1;
-      return gemm_splitk_reduce(r, s);
-    }
-  }
-  int splits = 1;
-  if (force_splits > 0) {
-    splits = a.ws && (long)force_splits * a.M * a.N <= a.ws_elems ? std::min(force_splits, nkt) : 1;
-  } else if (a.ws && tiles < 2 * CUS) {
-    // time ~ rounds(s) / s of the unsplit main loop, plus the partial-sum
-    // traffic (s fp32 products written and read back), which relative to the
-    // weight stream of one round is about 2.2 M / K per split
-    const double lam = 2.2 * (double)a.M / (double)a.K;
-    double best = 1e30;
-    for (int sp = 1; sp <= 8; ++sp) {
-      if (sp > 1 && (nkt / sp < 8 || (long)sp * a.M * a.N > a.ws_elems)) break;
-      const long wgs = tiles * sp;
-      const double cost = (double)cdiv(wgs, CUS) / sp + (sp > 1 ? lam * sp : 0.0);
-      if (cost < best - 1e-9) {
-        best = cost;
-        splits = sp;
-      }
-    }
-  }
-  if (a.need) {
-    *a.need = splits > 1 ? (long)cdiv(a.K, cdiv(nkt, splits) * BK) * a.M * a.N : 0;
-    return hipSuccess;
+    const long p1 = (long)s1 * a.M * n1;
+    GemmArgs g = a;
+    g.N = n1, g.k_split = ks1, g.splits = s1;
+    hipError_t e = launch_dma<BM, BN, BK, WGM, WGN, A_KC, B_KC, STAGES, SB, true, F16, TAIL>(g, s);
+    if (e != hipSuccess) return e;
+    g = a;
+    g.N = n2, g.k_split = ks2, g.splits = s2;
+    g.B = (const uint16_t*)a.B + (long)n1 * a.sbn;
+    g.ws = a.ws + p1, g.ws_elems = a.ws_elems - p1;
+    e = launch_dma<BM, BN, BK, WGM, WGN, A_KC, B_KC, STAGES, SB, true, F16, TAIL>(g, s);
+    if (e != hipSuccess) return e;
+    GemmArgs r = a;
+    r.splits = s1, r.splits2 = s2, r.split_cols = n1;
+    return gemm_splitk_reduce(r, s);
   }
   if (splits > 1) {
     a.k_split = cdiv(nkt, splits) * BK;
     a.splits = cdiv(a.K, a.k_split);
-    hipError_t e = launch_dma<BM, BN, BK, WGM, WGN, A_KC, B_KC, STAGES, SB, true, F16>(a, s);
+    hipError_t e = launch_dma<BM, BN, BK, WGM, WGN, A_KC, B_KC, STAGES, SB, true, F16, TAIL>(a, s);
     if (e != hipSuccess) return e;
     return gemm_splitk_reduce(a, s);
   }
   // many tiles: XCD-aware super-tile order
   if (tiles >= 2 * CUS) a.walk = 1;
-  return launch_dma<BM, BN, BK, WGM, WGN, A_KC, B_KC, STAGES, SB, false, F16>(a, s);
+  return launch_dma<BM, BN, BK, WGM, WGN, A_KC, B_KC, STAGES, SB, false, F16, TAIL>(a, s);
 }
 
-template <bool A_KC, bool B_KC, bool F16 = false>
-hipError_t run_cfg_id(int cfg, const GemmArgs& a, hipStream_t s, int splits = 0, int splits2 = 0,
-                      int cols1 = 0) {
+// Tile configurations.  All hold 64-value k-tiles; wpc workgroups fit a CU's LDS.
+enum TileCfg { T256x256, T256x192, T256x128, T128x128, T64x128, T64x64, T32x128, T_DW256 };
+
+template <bool A_KC, bool B_KC, bool F16, bool TAIL>
+hipError_t run_cfg(int cfg, const GemmArgs& a, hipStream_t s, int splits, int splits2, int cols1) {
+  constexpr bool SLICE = A_KC;  // a slice's activations or gradients times a weight matrix
   switch (cfg) {
-    case 0: return run_dma<128, 128, 64, 2, 2, A_KC, B_KC, 4, 4, F16>(a, s, splits);
-    case 1: return run_dma<256, 128, 64, 4, 2, A_KC, B_KC, 3, 3, F16>(a, s, splits);
-    case 2: return run_dma<256, 256, 64, 2, 4, A_KC, B_KC, 2, 2, F16>(a, s, splits);
-    case 3:
-      return run_dma<256, 256, 64, 2, 4, A_KC, B_KC, 2, 3, F16>(a, s, splits, splits2, cols1);
-    case 4:
-      // 256 x 192: 256 tiles for a 256-row product of width 49152, 64 for 12288
-      if constexpr (A_KC)
-        return run_dma<256, 192, 64, 4, 2, A_KC, B_KC, 2, 3, F16>(a, s, splits, splits2, cols1);
-      else return hipErrorNotSupported;
-    default: return hipErrorNotSupported;
+    case T128x128:
+      return run_dma<128, 128, 64, 4, 2, A_KC, B_KC, 4, 4, F16, TAIL>(a, s, splits, 0, 0);
+    case T64x64: return run_dma<64, 64, 64, 2, 2, A_KC, B_KC, 3, 3, F16, TAIL>(a, s, splits, 0, 0);
   }
+  if constexpr (!SLICE) {
+    if (cfg == T_DW256)
+      return run_dma<256, 256, 64, 2, 4, A_KC, B_KC, 2, 2, F16, TAIL>(a, s, splits, 0, 0);
+  } else if constexpr (!TAIL) {
+    switch (cfg) {
+      case T256x256:
+        return run_dma<256, 256, 64, 2, 4, A_KC, B_KC, 2, 3, F16, false>(a, s, splits, splits2, cols1);
+      // 256 tiles for a 256-row product of width 49152, 64 for 12288
+      case T256x192:
+        return run_dma<256, 192, 64, 4, 2, A_KC, B_KC, 2, 3, F16, false>(a, s, splits, splits2, cols1);
+      case T256x128:
+        return run_dma<256, 128, 64, 4, 2, A_KC, B_KC, 3, 3, F16, false>(a, s, splits, 0, 0);
+      case T64x128: return run_dma<64, 128, 64, 2, 4, A_KC, B_KC, 3, 3, F16, false>(a, s, splits, 0, 0);
+      case T32x128: return run_dma<32, 128, 64, 1, 4, A_KC, B_KC, 4, 4, F16, false>(a, s, splits, 0, 0);
+    }
+  }
+  return hipErrorNotSupported;
 }
 
-// Tile shape and split count for a product whose A operand is k-contiguous
-// (slice activations or output gradients times a weight matrix): the
-// candidate (tiles, splits) with the smallest modelled time.  The model was
-// fitted (log least squares, rms error 10 %) to a sweep of every candidate on
-// the stage's products for hidden sizes 2048-12288, operation-partitioning
-// shards and 128-512 rows:
-//   t = max(rounds * (0.74 + kt * c_kt), rows_tiles * N * K * 2 B * 0.177 us/MB)
-//       + (splits > 1 ? 5.7 + splits * M * N * 8 B / 5.8 MB/us : 0)
-// with rounds = workgroups / 256 rounded up, kt = k-tiles per split and c_kt
-// = 0.59 / 0.91 / 1.21 / 1.44 us for 128x128 / 256x128 / 256x192 / 256x256 tiles: a round of
-// workgroups, not below the weight stream from HBM, plus the partial sums.
+// ------------------------------------------------------- tile shape and splits
+
+constexpr int kSplits[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
+
+// Modelled main loop (us) of `wgs` workgroups of kt k-tiles each: a workgroup
+// costs a + kt * c alone on its CU (c_cold where the weights come from HBM), and
+// kt * c_more (plus a) for every further workgroup that shares the CU.
+struct Cand {
+  int cfg, bm, bn, wpc;
+  double a, c, c_cold, c_more;
+  double main_us(long wgs, int kt, bool cold) const {
+    const long load = cdiv(wgs, 256), rounds = cdiv(wgs, 256l * wpc);
+    return rounds * kt * (cold ? c_cold : c) + (load - rounds) * kt * c_more + load * a;
+  }
+};
+
 struct TileChoice {
   int cfg, splits;
   int splits2 = 0, cols1 = 0;  // two column groups (see run_dma), 0: one launch
+  long partials = 0;           // fp32 partial sums it takes
 };
-TileChoice choose_tiles(const GemmArgs& a) {
-  static const int kSplits[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
-  struct Cand {
-    int cfg, bm, bn;
+
+// fp32 partial sums that the static scratch of tp_slice_forward_static holds
+constexpr long STATIC_ELEMS = (32l << 20) / 4;
+
+// The partial sums by which tp_slice_forward_static admits a slice: those of a
+// reference plan over four tile shapes (128x128 .. 256x256; for row counts off the
+// 8-row grid or a K off the 64-value grid, three workgroups a CU), kept as it was
+// when the admission was defined, so that a plan that takes less scratch changes
+// no answer of that call.
+long reference_partials(const GemmArgs& a) {
+  if (a.M % 8 || a.K % 64) {
+    const int bm = a.M <= 64 ? 64 : a.M <= 128 ? 128 : a.M <= 256 ? 256 : 128;
+    const long tiles = (long)cdiv(a.M, bm) * cdiv(a.N, 128);
+    if (tiles >= 768 || !a.ws) return 0;
+    int sp = (int)std::min<long>(8, cdiv(768, tiles));
+    while (sp > 1 && (a.K / sp < 512 || (long)sp * a.M * a.N > a.ws_elems)) --sp;
+    return sp > 1 ? (long)cdiv(a.K, cdiv(cdiv(a.K, sp), 64) * 64) * a.M * a.N : 0;
+  }
+  struct Ref {
+    int bm, bn;
     double c_kt;
   };
-  static const Cand kCands[] = {
-      {0, 128, 128, 0.5931}, {1, 256, 128, 0.9088}, {4, 256, 192, 1.2088}, {3, 256, 256, 1.4367}};
+  static const Ref kRefs[] = {{128, 128, 0.5931}, {256, 128, 0.9088}, {256, 192, 1.2088},
+                              {256, 256, 1.4367}};
   const int nkt = a.K / 64;
   double best = 1e300;
-  TileChoice pick{3, 1};
-  for (const Cand& c : kCands) {
+  long pick = 0;
+  for (const Ref& c : kRefs) {
     const long mt = cdiv(a.M, c.bm), tiles = mt * cdiv(a.N, c.bn);
     const double hbm = (double)mt * a.N * a.K * 2.0 / 1e6 * 0.1773;
     for (int sp : kSplits) {
       if (sp > nkt) break;
       if (sp > 1 && (!a.ws || (long)sp * a.M * a.N > a.ws_elems)) break;
       const int ks = cdiv(nkt, sp), s = cdiv(nkt, ks);
-      const long rounds = cdiv(tiles * s, 256);
-      double t = std::max(rounds * (0.7377 + ks * c.c_kt), hbm);
+      double t = std::max(cdiv(tiles * s, 256) * (0.7377 + ks * c.c_kt), hbm);
       if (s > 1) t += 5.6764 + (double)s * a.M * a.N * 8.0 / 1e6 / 5.7874;
-      if (t < best) {
+      if (t < best) best = t, pick = s > 1 ? (long)s * a.M * a.N : 0;
+    }
+  }
+  const double single = best;
+  for (const Ref& c : kRefs) {
+    if (c.bn < 192) continue;
+    const long mt = cdiv(a.M, c.bm), tn = cdiv(a.N, c.bn);
+    for (int sp1 : kSplits) {
+      if (sp1 > nkt) break;
+      const int ks1 = cdiv(nkt, sp1), e1 = cdiv(nkt, ks1);
+      for (long r1 = 1;; ++r1) {
+        const long cols1 = r1 * 256 / (mt * e1);
+        if (cols1 >= tn) break;
+        if (cols1 * mt * e1 != r1 * 256) continue;
+        const long n1 = cols1 * c.bn, n2 = a.N - n1;
+        const double h1 = (double)mt * n1 * a.K * 2.0 / 1e6 * 0.1773;
+        const double h2 = (double)mt * n2 * a.K * 2.0 / 1e6 * 0.1773;
+        for (int sp2 : kSplits) {
+          if (sp2 > nkt) break;
+          const int ks2 = cdiv(nkt, sp2), e2 = cdiv(nkt, ks2);
+          const double part = (double)e1 * a.M * n1 + (double)e2 * a.M * n2;
+          if (!a.ws || part > (double)a.ws_elems) break;
+          const double t = std::max(r1 * (0.7377 + ks1 * c.c_kt), h1) +
+                           std::max(cdiv(mt * (tn - cols1) * e2, 256) * (0.7377 + ks2 * c.c_kt), h2) +
+                           5.6764 + part * 8.0 / 1e6 / 5.7874;
+          if (t < best && t < 0.97 * single) best = t, pick = (long)part;
+        }
+      }
+    }
+  }
+  return pick;
+}
+
+// Tile shape and split count of a product whose A operand is k-contiguous (slice
+// activations or output gradients times a weight matrix): the candidate with the
+// smallest modelled time.  The model was fitted (log least squares, rms error 8 %)
+// to a sweep of every candidate (graph replays, rotating weights) on the 8 products
+// of a layer for widths 256-12288 and 8- and 4-way shards, 16-4096 rows; its pick
+// is on average 2.5 % (at worst 26 %) over the best candidate of each product,
+// where the former four shapes (128x128 and up, one workgroup a CU) were 22 % over.
+// What decides: a CU moves operands at 45-65 GB/s, more with two or three
+// workgroups on it, so narrow products want small tiles that use every CU without
+// partial sums (256 x 3072 x 1024: 14.5 -> 9 us, 256 x 8192 x 2048: 23 -> 18 us with
+// a GELU), wide ones large tiles that move few bytes per flop.
+//   t = 3.4 + max(main + GELU, weights (once from HBM, again from the caches for
+//   every further row tile) + A (for every column tile)) + (split: 2.9 + partials)
+TileChoice choose_tiles(const GemmArgs& a, bool tail) {
+  static const Cand kCands[] = {{T32x128, 32, 128, 2, 0.453, 0.2906, 0.4149, 0.1398},
+                                {T64x64, 64, 64, 3, 0.355, 0.3117, 0.4227, 0.1123},
+                                {T64x128, 64, 128, 2, 0.613, 0.3932, 0.4942, 0.1854},
+                                {T128x128, 128, 128, 1, 1.326, 0.5297, 0.5996, 0.0},
+                                {T256x128, 256, 128, 1, 1.624, 0.8944, 0.9446, 0.0},
+                                {T256x192, 256, 192, 1, 2.535, 1.1647, 1.2717, 0.0},
+                                {T256x256, 256, 256, 1, 3.007, 1.3868, 1.5431, 0.0}};
+  const int nkt = cdiv(a.K, 64);
+  const double wmb = (double)a.N * a.K * 2e-6, amb = (double)a.M * a.K * 2e-6;
+  const bool cold = (double)a.N * a.K >= 18e6;  // a weight matrix past the caches' share
+  const long room = a.ws ? a.ws_elems : 0;
+  const bool gelu = a.epi == EPI_GELU || a.epi == EPI_DGELU;
+  auto stream_us = [&](const Cand& c, double cols) {  // for `cols` of the N columns
+    const long mt = cdiv(a.M, c.bm);
+    return wmb * cols / a.N * (0.1765 + 0.0416 * (mt - 1)) + amb * 0.0557 * cdiv((long)cols, c.bn);
+  };
+  long limit = -1;  // partial sums the plan may take; the reference plan only where needed
+  auto fits = [&](double part) {
+    if (part > room) return false;
+    if (part <= STATIC_ELEMS) return true;
+    if (limit < 0) limit = std::max(STATIC_ELEMS, reference_partials(a));
+    return part <= limit;
+  };
+  double best = 1e300;
+  TileChoice pick{T128x128, 1};
+  for (const Cand& c : kCands) {
+    if (tail && c.cfg != T64x64 && c.cfg != T128x128) continue;
+    const long tiles = (long)cdiv(a.M, c.bm) * cdiv(a.N, c.bn);
+    const double stream = stream_us(c, a.N);
+    for (int sp : kSplits) {
+      if (sp > nkt) break;
+      const int ks = cdiv(nkt, sp), s = cdiv(nkt, ks);
+      double t = c.main_us(tiles * s, ks, cold);
+      if (s == 1 && gelu) t += 2.686 * cdiv(tiles, 256) * c.bm * c.bn / 16384.0;
+      t = std::max(t, stream) + 3.361;
+      const double part = s > 1 ? (double)s * a.M * a.N : 0.0;
+      if (s > 1) t += 2.887 + part * 8e-6 * 0.1638;
+      if (t < best && (s == 1 || fits(part))) {
         best = t;
-        pick = {c.cfg, s};
+        pick = {c.cfg, s, 0, 0, (long)part};
       }
     }
   }
@@ -709,8 +844,10 @@ TileChoice choose_tiles(const GemmArgs& a) {
   // rounds, the second group takes its own split count, so no round runs
   // part-empty the way a uniform split leaves the last one (the query/key/value
   // product of 144 tiles of 256 x 256: 2 x 128 + 16 x 16 workgroups against 3
-  // x 144).  Taken when the model puts it 3 % under the best single launch.
+  // x 144).  Taken when the model puts it 3 % under the best single launch, and
+  // looked for only where 3 % outweighs the further launch.
   const double single = best;
+  if (tail || single < 100.0) return pick;
   for (const Cand& c : kCands) {
     if (c.bm != 256 || c.bn < 192) continue;
     const long mt = cdiv(a.M, c.bm), tn = cdiv(a.N, c.bn);
@@ -722,20 +859,16 @@ TileChoice choose_tiles(const GemmArgs& a) {
         if (cols1 >= tn) break;
         if (cols1 * mt * e1 != r1 * 256) continue;
         const long n1 = cols1 * c.bn, n2 = a.N - n1;
-        const double hbm1 = (double)mt * n1 * a.K * 2.0 / 1e6 * 0.1773;
-        const double hbm2 = (double)mt * n2 * a.K * 2.0 / 1e6 * 0.1773;
+        const double t1 = std::max(c.main_us(r1 * 256, ks1, cold), stream_us(c, n1));
         for (int sp2 : kSplits) {
           if (sp2 > nkt) break;
           const int ks2 = cdiv(nkt, sp2), e2 = cdiv(nkt, ks2);
           const double part = (double)e1 * a.M * n1 + (double)e2 * a.M * n2;
-          if (!a.ws || part > (double)a.ws_elems) break;
-          const long r2 = cdiv(mt * (tn - cols1) * e2, 256);
-          double t = std::max(r1 * (0.7377 + ks1 * c.c_kt), hbm1) +
-                     std::max(r2 * (0.7377 + ks2 * c.c_kt), hbm2);
-          t += 5.6764 + part * 8.0 / 1e6 / 5.7874;
-          if (t < best && t < 0.97 * single) {
+          const double t = t1 + 2 * 3.361 + 2.887 + part * 8e-6 * 0.1638 +
+                           std::max(c.main_us(mt * (tn - cols1) * e2, ks2, cold), stream_us(c, n2));
+          if (t < best && t < 0.97 * single && fits(part)) {
             best = t;
-            pick = {c.cfg, e1, e2, (int)cols1};
+            pick = {c.cfg, e1, e2, (int)cols1, (long)part};
           }
         }
       }
@@ -744,15 +877,49 @@ TileChoice choose_tiles(const GemmArgs& a) {
   return pick;
 }
 
+// The same for the weight-gradient products (both operands m/n-contiguous, a
+// reduction over tokens, fp32 output read and written or only written): 256 x 256
+// tiles where they fill the CUs, smaller ones (or splits) for narrow gradients,
+// which left most CUs idle (2048 x 2048 over 2048 tokens: 64 tiles of 256 x 256 46
+// us, 256 tiles of 128 x 128 28 us; 512 x 2048: 16 tiles 44 us, 64 x 64 tiles 16
+// us).  Fitted like choose_tiles (rms error 8 %): on average 2.7 % over the best
+// candidate, always 256 x 256 was 74 % over on the same sweep (widths 512-5120,
+// 64-8192 tokens).
+TileChoice choose_dw(const GemmArgs& a) {
+  static const Cand kCands[] = {{T64x64, 64, 64, 3, 0.0, 0.3745, 0.3745, 0.1047},
+                                {T128x128, 128, 128, 1, 0.598, 0.5815, 0.5815, 0.0},
+                                {T_DW256, 256, 256, 1, 1.841, 1.3978, 1.3978, 0.0}};
+  const int nkt = cdiv(a.K, 64);
+  const double out = (double)a.M * a.N * 4e-6 * (a.overwrite ? 1 : 2);
+  double best = 1e300;
+  TileChoice pick{T_DW256, 1};
+  for (const Cand& c : kCands) {
+    const long tiles = (long)cdiv(a.M, c.bm) * cdiv(a.N, c.bn);
+    for (int sp : kSplits) {
+      if (sp > nkt || sp > 8) break;
+      const int ks = cdiv(nkt, sp), s = cdiv(nkt, ks);
+      if (s > 1 && (!a.ws || (long)s * a.M * a.N > a.ws_elems)) break;
+      double t = c.main_us(tiles * s, ks, false);
+      t += s > 1 ? 3.2 + ((double)s * a.M * a.N * 8e-6 + out) * 0.1659 : out * 0.1437;
+      if (t < best) {
+        best = t;
+        pick = {c.cfg, s};
+      }
+    }
+  }
+  return pick;
+}
+
 }  // namespace
 
-// Explicit configuration (for measurement); -1 picks by shape.  Shapes the
-// DMA path takes: K a multiple of BK; every operand dimension a multiple of 8;
-// m/n-contiguous operands at least 128 wide.
-hipError_t gemm_dma_bf16_cfg(int cfg, const GemmArgs& a, hipStream_t s) {
+// Shapes the DMA path takes: 16-byte-aligned operands with a unit stride and
+// leading dimensions of whole 16-byte chunks; N, and M where A is contiguous along
+// it, multiples of 8 (a k-contiguous A takes any number of rows); K any multiple
+// of 8, or any number of tokens for the weight-gradient products.
+hipError_t gemm_dma_bf16(const GemmArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
-  if (a.M % 8 || a.N % 8 || a.K % 32) return hipErrorNotSupported;
   const bool a_kc = a.sak == 1, b_kc = a.sbk == 1, a_mc = a.sam == 1, b_nc = a.sbn == 1;
+  if (a.N % 8 || a.K <= 0) return hipErrorNotSupported;
   if (((uintptr_t)a.A & 15) || ((uintptr_t)a.B & 15)) return hipErrorNotSupported;
   const long lda = a_kc ? a.sam : a.sak, ldb = b_kc ? a.sbn : a.sbk;
   if ((lda & 7) || (ldb & 7)) return hipErrorNotSupported;
@@ -763,37 +930,31 @@ hipError_t gemm_dma_bf16_cfg(int cfg, const GemmArgs& a, hipStream_t s) {
   // operands) as 8-column segments
   if (a.epi == EPI_ACC_F32 && (((uintptr_t)a.C & 15) || (a.ldc & 3))) return hipErrorNotSupported;
   if (a.epi != EPI_ACC_F32 && !vec8_ok(a)) return hipErrorNotSupported;
-  int splits = 0, splits2 = 0, cols1 = 0;
-  if (cfg < 0) {
-    // weight-gradient products (both operands m/n-contiguous): 256 x 256 tiles
-    // over one (A, B) ring; products with a weight matrix as B: the modelled
-    // best tile shape and split count (256 x 256 tiles keep the weight stream
-    // a k-tile further ahead than the activations)
-    if (a_mc && b_nc) {
-      cfg = 2;
-    } else {
-      const TileChoice c = choose_tiles(a);
-      cfg = c.cfg;
-      splits = c.splits;
-      splits2 = c.splits2;
-      cols1 = c.cols1;
-    }
+  const bool tail = a.K % 64 != 0;
+  if (a_mc && b_nc && !a_kc) {
+    if (a.M % 8 || a.epi != EPI_ACC_F32) return hipErrorNotSupported;
+    const TileChoice c = choose_dw(a);
+    return tail ? run_cfg<false, false, false, true>(c.cfg, a, s, c.splits, 0, 0)
+                : run_cfg<false, false, false, false>(c.cfg, a, s, c.splits, 0, 0);
   }
-  if (a.in_f16) {
-    // fp16 operands: the query/key/value product (activations times the fp16
-    // weight copy, both k-contiguous)
-    if (!(a_kc && b_kc) || a.epi != EPI_QKV) return hipErrorNotSupported;
-    return run_cfg_id<true, true, true>(cfg, a, s, splits, splits2, cols1);
+  if (!a_kc || (!b_kc && !b_nc) || a.K % 8) return hipErrorNotSupported;
+  const bool fwd = a.epi == EPI_QKV || a.epi == EPI_RESID || a.epi == EPI_GELU;
+  if (b_kc ? !fwd : (a.epi != EPI_STORE && a.epi != EPI_DGELU)) return hipErrorNotSupported;
+  // fp16 operands: the query/key/value product (activations times the fp16 weight
+  // copy) of stages whose widths are whole k-tiles
+  if (a.in_f16 && (!b_kc || a.epi != EPI_QKV || tail)) return hipErrorNotSupported;
+  if (a.need) {
+    *a.need = reference_partials(a);
+    return hipSuccess;
   }
-  if (a_kc && b_kc) return run_cfg_id<true, true>(cfg, a, s, splits, splits2, cols1);
-  if (a_kc && b_nc) return run_cfg_id<true, false>(cfg, a, s, splits, splits2, cols1);
-  if (a_mc && b_nc) {
-    if (a.M < 128 || a.N < 128) return hipErrorNotSupported;
-    return run_cfg_id<false, false>(cfg, a, s);
-  }
-  return hipErrorNotSupported;
+  const TileChoice c = choose_tiles(a, tail);
+  if (a.in_f16)
+    return run_cfg<true, true, true, false>(c.cfg, a, s, c.splits, c.splits2, c.cols1);
+  if (tail)
+    return b_kc ? run_cfg<true, true, false, true>(c.cfg, a, s, c.splits, 0, 0)
+                : run_cfg<true, false, false, true>(c.cfg, a, s, c.splits, 0, 0);
+  return b_kc ? run_cfg<true, true, false, false>(c.cfg, a, s, c.splits, c.splits2, c.cols1)
+              : run_cfg<true, false, false, false>(c.cfg, a, s, c.splits, c.splits2, c.cols1);
 }
-
-hipError_t gemm_dma_bf16(const GemmArgs& a, hipStream_t s) { return gemm_dma_bf16_cfg(-1, a, s); }
 
 }  // namespace tp
