@@ -5,6 +5,8 @@
 #include "tp_epilogue.hpp"
 #include "tp_kernels.hpp"
 
+#include <algorithm>
+
 namespace tp {
 
 // ------------------------------------------------------------- generic GEMM
@@ -246,100 +248,104 @@ __global__ __launch_bounds__(1024) void ln_bwd_kernel(int H, const T* du, const 
   }
 }
 
-// Column reductions over n rows.  A block owns 32 columns (4 chunks of 8) and
-// 64 row groups; row group rg sums rows rg, rg + 64, ... in order, loading four
-// rows at a time, then the 64 partial sums of a column are added as 8 in-order
-// groups of 8, the group sums in order.  Deterministic.
-constexpr int CR_RG = 64, CR_COLS = 32, CR_UNROLL = 4;
+// Column reductions over rows: every bias and LayerNorm-parameter gradient of a
+// layer in one launch.  A block owns 64 columns (8 chunks of 8: whole 128-byte
+// lines of a bf16 row) of one job and one chunk of the rows; row group rg (of 32)
+// sums rows rg, rg + 32, ... of the chunk in order, loading four rows at a time, then
+// a column's 32 partial sums are added as 4 in-order groups of 8, the group sums in
+// order.  With more than one row chunk the chunk sums go to `part` and a second
+// launch adds them in order.  Deterministic.
+// Bound by memory once enough blocks are in flight (11 H / 64 column blocks a layer
+// are 352 at width 2048): one launch per tensor with 64-byte row pieces and no row
+// split had H / 32 = 64 blocks for most tensors.  A layer's reductions, 2048 wide:
+// 2048 tokens 104 -> 40 us, 8192 rows 381 -> 131 us (4 TB/s); 1024 wide, 256 tokens
+// 21 us in 6 launches -> 8 us in one; 12288 wide, 2048 tokens 238 -> 168 us (4.5 TB/s).
+constexpr int CR_RG = 32, CR_COLS = 64, CR_UNROLL = 4;
 
-// Adds the 64 per-row-group partials of each of the block's 32 columns (in
-// p[rg][col]) and returns the column total in threads 0..31.
-__device__ inline float col_partials_sum(float (*p)[CR_COLS + 1], float* q /* 8 x 33 */) {
-  const int col = threadIdx.x & 31, grp = threadIdx.x >> 5;
+// The column totals of p[rg][col], in threads 0..63.
+__device__ inline float col_partials_sum(float (*p)[CR_COLS + 1], float (*q)[CR_COLS]) {
+  const int col = threadIdx.x & 63, grp = threadIdx.x >> 6;
   float s = 0.f;
 #pragma unroll
   for (int i = 0; i < 8; ++i) s += p[grp * 8 + i][col];
-  q[grp * (CR_COLS + 1) + col] = s;
+  q[grp][col] = s;
   __syncthreads();
   float t = 0.f;
   if (threadIdx.x < CR_COLS)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) t += q[i * (CR_COLS + 1) + col];
+    for (int i = 0; i < 4; ++i) t += q[i][col];
   return t;
 }
 
+// Partial (or final) sum of one output column; slot: its column in `part`.
+__device__ inline void col_out(const ColJobs& J, float* out, int col, int slot, float s) {
+  if (J.chunks > 1)
+    J.part[(long)blockIdx.y * J.slots + slot] = s;
+  else
+    out[col] = J.store ? s : out[col] + s;
+}
+
+// T: stage dtype; TX: type of the LayerNorm input rows
 template <typename T, typename TX>
-__global__ __launch_bounds__(256) void ln_param_grads_kernel(int n, int H, const T* du,
-                                                             const TX* x, const float* mean,
-                                                             const float* rstd, float* dg,
-                                                             float* db, int store) {
-  __shared__ float pg[CR_RG][CR_COLS + 1], pb[CR_RG][CR_COLS + 1], q[2][8 * (CR_COLS + 1)];
-  const int cc = threadIdx.x & 3, rg = threadIdx.x >> 2;
-  const int c0 = blockIdx.x * CR_COLS + cc * 8;
-  float sg[8] = {}, sb[8] = {};
-  if (c0 < H) {
-    for (int t0 = rg; t0 < n; t0 += CR_UNROLL * CR_RG) {
+__global__ __launch_bounds__(256) void col_reduce_kernel(ColJobs J) {
+  __shared__ float pa[CR_RG][CR_COLS + 1], pb[CR_RG][CR_COLS + 1], q[2][4][CR_COLS];
+  int ji = 0;
+  while (ji + 1 < J.count && (int)blockIdx.x >= J.job[ji + 1].block0) ++ji;
+  const ColJob& j = J.job[ji];
+  const int cc = threadIdx.x & 7, rg = threadIdx.x >> 3;
+  const int col0 = (blockIdx.x - j.block0) * CR_COLS, c0 = col0 + cc * 8;
+  const int r0 = blockIdx.y * J.rows_per, r1 = min(J.rows, r0 + J.rows_per);
+  float sa[8] = {}, sb[8] = {};
+  if (c0 < j.cols) {
+    const T* A = (const T*)j.a + c0;
+    const TX* X = j.x ? (const TX*)j.x + c0 : nullptr;
+    for (int t0 = r0 + rg; t0 < r1; t0 += CR_UNROLL * CR_RG) {
       float d[CR_UNROLL][8], xv[CR_UNROLL][8], mu[CR_UNROLL], rs[CR_UNROLL];
 #pragma unroll
       for (int k = 0; k < CR_UNROLL; ++k) {
         const int t = t0 + k * CR_RG;
-        if (t < n) {
-          load8(du + (long)t * H + c0, d[k]);
-          load8(x + (long)t * H + c0, xv[k]);
-          mu[k] = mean[t], rs[k] = rstd[t];
+        if (t < r1) {
+          load8(A + (long)t * j.lda, d[k]);
+          if (X) {
+            load8(X + (long)t * j.lda, xv[k]);
+            mu[k] = j.mean[t], rs[k] = j.rstd[t];
+          }
         }
       }
 #pragma unroll
       for (int k = 0; k < CR_UNROLL; ++k)
-        if (t0 + k * CR_RG < n)
+        if (t0 + k * CR_RG < r1)
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
-            sg[e] += d[k][e] * ((xv[k][e] - mu[k]) * rs[k]);
-            sb[e] += d[k][e];
+            sa[e] += d[k][e];
+            if (X) sb[e] += d[k][e] * ((xv[k][e] - mu[k]) * rs[k]);
           }
     }
   }
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    pg[rg][cc * 8 + e] = sg[e];
-    pb[rg][cc * 8 + e] = sb[e];
-  }
+  for (int e = 0; e < 8; ++e) pa[rg][cc * 8 + e] = sa[e], pb[rg][cc * 8 + e] = sb[e];
   __syncthreads();
-  const float a = col_partials_sum(pg, q[0]);
-  const float b = col_partials_sum(pb, q[1]);
-  const int col = blockIdx.x * CR_COLS + threadIdx.x;
-  if (threadIdx.x < CR_COLS && col < H) {
-    dg[col] = store ? a : dg[col] + a;
-    db[col] = store ? b : db[col] + b;
+  const float a = col_partials_sum(pa, q[0]);
+  const float b = j.x ? col_partials_sum(pb, q[1]) : 0.f;  // uniform per block
+  const int col = col0 + threadIdx.x;
+  if (threadIdx.x < CR_COLS && col < j.cols) {
+    col_out(J, j.sum, col, j.slot0 + col, a);
+    if (j.x) col_out(J, j.xsum, col, j.slot0 + j.cols + col, b);
   }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void colsum_kernel(int n, int N, const T* A, long lda,
-                                                     float* out, int store) {
-  __shared__ float ps[CR_RG][CR_COLS + 1], q[8 * (CR_COLS + 1)];
-  const int cc = threadIdx.x & 3, rg = threadIdx.x >> 2;
-  const int c0 = blockIdx.x * CR_COLS + cc * 8;
-  float s[8] = {};
-  if (c0 < N) {
-    for (int t0 = rg; t0 < n; t0 += CR_UNROLL * CR_RG) {
-      float v[CR_UNROLL][8];
-#pragma unroll
-      for (int k = 0; k < CR_UNROLL; ++k)
-        if (t0 + k * CR_RG < n) load8(A + (long)(t0 + k * CR_RG) * lda + c0, v[k]);
-#pragma unroll
-      for (int k = 0; k < CR_UNROLL; ++k)
-        if (t0 + k * CR_RG < n)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) s[e] += v[k][e];
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) ps[rg][cc * 8 + e] = s[e];
-  __syncthreads();
-  const float a = col_partials_sum(ps, q);
-  const int col = blockIdx.x * CR_COLS + threadIdx.x;
-  if (threadIdx.x < CR_COLS && col < N) out[col] = store ? a : out[col] + a;
+// Adds the row chunks' partial sums in order; one thread per output column.
+__global__ __launch_bounds__(256) void col_finish_kernel(ColJobs J) {
+  const int slot = blockIdx.x * 256 + threadIdx.x;
+  if (slot >= J.slots) return;
+  int ji = 0;
+  while (ji + 1 < J.count && slot >= J.job[ji + 1].slot0) ++ji;
+  const ColJob& j = J.job[ji];
+  float s = 0.f;
+  for (int c = 0; c < J.chunks; ++c) s += J.part[(long)c * J.slots + slot];
+  const int col = slot - j.slot0;
+  float* out = col < j.cols ? j.sum + col : j.xsum + (col - j.cols);
+  *out = J.store ? s : *out + s;
 }
 
 // dK and dV (fp32, [n, H]) into the K and V thirds of the dQKV rows, 8
@@ -411,21 +417,36 @@ hipError_t ln_bwd(int dtype, int n, int H, const void* du, const void* x, int x_
   return hipGetLastError();
 }
 
-hipError_t ln_param_grads(int dtype, int n, int H, const void* du, const void* x, int x_f32,
-                          const float* mean, const float* rstd, float* dg, float* db, int store,
-                          hipStream_t s) {
+hipError_t col_reduce(int dtype, int x_f32, ColJobs J, hipStream_t s) {
   clear_stale_error();
-  if (n <= 0) return hipSuccess;
-  const int blocks = cdiv(H, CR_COLS);
+  if (J.rows <= 0 || J.count <= 0) return hipSuccess;
+  int blocks = 0, slots = 0;
+  for (int i = 0; i < J.count; ++i) {
+    ColJob& j = J.job[i];
+    j.block0 = blocks, j.slot0 = slots;
+    blocks += cdiv(j.cols, CR_COLS);
+    slots += j.cols * (j.x ? 2 : 1);
+  }
+  J.slots = slots;
+  // about 1024 blocks (4 per CU), at most 16 chunks of at least 256 rows (of a
+  // 256-row slice, two chunks and their second launch took 10 us for 8); the
+  // partials must fit
+  J.chunks = (int)std::min<long>({16, cdiv(J.rows, 256), std::max(1, cdiv(1024, blocks))});
+  while (J.chunks > 1 && (!J.part || (long)J.chunks * slots > J.part_elems)) --J.chunks;
+  J.rows_per = cdiv(J.rows, J.chunks);
+  J.chunks = cdiv(J.rows, J.rows_per);
+  const dim3 grid(blocks, J.chunks);
   if (dtype == DT_FP32)
-    ln_param_grads_kernel<float, float><<<blocks, 256, 0, s>>>(n, H, (const float*)du,
-                                                               (const float*)x, mean, rstd, dg, db, store);
+    col_reduce_kernel<float, float><<<grid, 256, 0, s>>>(J);
   else if (x_f32)
-    ln_param_grads_kernel<bf16, float><<<blocks, 256, 0, s>>>(n, H, (const bf16*)du,
-                                                              (const float*)x, mean, rstd, dg, db, store);
+    col_reduce_kernel<bf16, float><<<grid, 256, 0, s>>>(J);
   else
-    ln_param_grads_kernel<bf16, bf16><<<blocks, 256, 0, s>>>(n, H, (const bf16*)du,
-                                                             (const bf16*)x, mean, rstd, dg, db, store);
+    col_reduce_kernel<bf16, bf16><<<grid, 256, 0, s>>>(J);
+  if (J.chunks > 1) {
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    col_finish_kernel<<<cdiv(slots, 256), 256, 0, s>>>(J);
+  }
   return hipGetLastError();
 }
 
@@ -461,18 +482,6 @@ hipError_t cvt_bf16_f16(size_t n, const void* src, void* dst, hipStream_t s) {
   const size_t work = vec ? n / 8 : n;
   const int blocks = (int)((work + 255) / 256 < 8192 ? (work + 255) / 256 : 8192);
   cvt_bf16_f16_kernel<<<blocks, 256, 0, s>>>(n, (const uint16_t*)src, (uint16_t*)dst, vec);
-  return hipGetLastError();
-}
-
-hipError_t colsum_acc(int dtype, int n, int N, const void* A, long lda, float* out, int store,
-                      hipStream_t s) {
-  clear_stale_error();
-  if (n <= 0 || N <= 0) return hipSuccess;
-  const int blocks = cdiv(N, CR_COLS);
-  if (dtype == DT_FP32)
-    colsum_kernel<float><<<blocks, 256, 0, s>>>(n, N, (const float*)A, lda, out, store);
-  else
-    colsum_kernel<bf16><<<blocks, 256, 0, s>>>(n, N, (const bf16*)A, lda, out, store);
   return hipGetLastError();
 }
 

@@ -338,32 +338,39 @@ tp_status wgrad_gemms(tp_stage* S, int li, int l, int n) {
   return TP_OK;
 }
 
-// DEFERRED mode: bias and LayerNorm-parameter gradients of layer li as column
-// reductions over all rows [0, rows) of the kept per-token gradients.
-tp_status deferred_param_reductions(tp_stage* S, int li, int rows) {
-  const int H = S->H, A = S->A, F = S->F, dt = S->dt;
+// Bias and LayerNorm-parameter gradients of layer li: column sums over rows
+// [row0, row0 + rows) of the kept per-token gradients (du2, du: the LayerNorm output
+// gradients of those rows).
+tp_status param_reductions(tp_stage* S, int li, int row0, int rows, const void* du2,
+                           const void* du) {
+  const int H = S->H, A = S->A, F = S->F;
   const size_t e = S->esz;
-  const double nb = (double)rows * H * e;
-  hipStream_t st = S->stream;
   LayerBufs& B = S->lb[li];
   tp_layer_ptrs& G = S->G[li];
-  const int ow = S->grad_store;
-  TRY(launch(S, K_MISC, 0, nb,
-             [&] { return colsum_acc(dt, rows, H, B.dy, H, (float*)G.b_fc2, ow, st); }));
-  TRY(launch(S, K_MISC, 0, (double)rows * F * e,
-             [&] { return colsum_acc(dt, rows, F, B.dz, F, (float*)G.b_fc1, ow, st); }));
-  TRY(launch(S, K_NORM, 0, 2 * nb, [&] {
-    return ln_param_grads(dt, rows, H, B.du2, B.x1, S->mixed, B.mean2, B.rstd2, (float*)G.ln2_g,
-                          (float*)G.ln2_b, ow, st);
-  }));
-  TRY(launch(S, K_MISC, 0, nb,
-             [&] { return colsum_acc(dt, rows, H, B.dx1, H, (float*)G.b_o, ow, st); }));
-  TRY(launch(S, K_MISC, 0, 3.0 * rows * A * e,
-             [&] { return colsum_acc(dt, rows, 3 * A, B.dqkv, 3 * A, (float*)G.b_qkv, ow, st); }));
-  TRY(launch(S, K_NORM, 0, 2 * nb, [&] {
-    return ln_param_grads(dt, rows, H, B.du, B.x_in, S->mixed, B.mean1, B.rstd1, (float*)G.ln1_g,
-                          (float*)G.ln1_b, ow, st);
-  }));
+  auto bias = [&](const void* a, int cols, void* out) {
+    ColJob j;
+    j.a = a, j.cols = cols, j.lda = cols, j.sum = (float*)out;
+    return j;
+  };
+  auto norm = [&](const void* a, const void* x, const float* mean, const float* rstd, void* g,
+                  void* b) {
+    ColJob j = bias(a, H, b);
+    j.x = x, j.mean = mean, j.rstd = rstd, j.xsum = (float*)g;
+    return j;
+  };
+  ColJobs J;
+  J.job[0] = bias(rowp(B.dy, row0, H, e), H, G.b_fc2);
+  J.job[1] = bias(rowp(B.dz, row0, F, e), F, G.b_fc1);
+  J.job[2] = norm(du2, rowp(B.x1, row0, H, S->resz), B.mean2 + row0, B.rstd2 + row0, G.ln2_g,
+                  G.ln2_b);
+  J.job[3] = bias(rowp(B.dx1, row0, H, e), H, G.b_o);
+  J.job[4] = bias(rowp(B.dqkv, row0, 3 * A, e), 3 * A, G.b_qkv);
+  J.job[5] = norm(du, rowp(B.x_in, row0, H, S->resz), B.mean1 + row0, B.rstd1 + row0, G.ln1_g,
+                  G.ln1_b);
+  J.count = 6, J.rows = rows, J.store = S->grad_store;
+  J.part = S->sc.splitk, J.part_elems = (long)S->sc.splitk_elems;
+  TRY(launch(S, K_MISC, 0, (double)rows * ((4.0 * H + F + 3.0 * A) * e + 2.0 * H * S->resz),
+             [&] { return col_reduce(S->dt, S->mixed, J, S->stream); }));
   return TP_OK;
 }
 
@@ -456,11 +463,9 @@ tp_status backward_impl(tp_stage* S, int l, int r, const void* dy, void* dx) {
   const bool per_slice = S->cfg.wgrad_mode == TP_WGRAD_PER_SLICE;
   const double nb = (double)n * H * e;
   const bool mx = S->mixed;
-  const int ow = S->grad_store;
   for (int li = NL - 1; li >= 0; --li) {
     LayerBufs& B = S->lb[li];
     const tp_layer_ptrs& P = S->P[li];
-    tp_layer_ptrs& G = S->G[li];
     void* dyl = rowp(B.dy, lr, H, e);
     const void* x1 = rowp(B.x1, lr, H, S->resz);
     const void* xin = rowp(B.x_in, lr, H, S->resz);
@@ -470,8 +475,6 @@ tp_status backward_impl(tp_stage* S, int l, int r, const void* dy, void* dx) {
     GemmArgs g = nn(n, F, H, dyl, H, P.w_fc2);
     g.epi = EPI_DGELU, g.R = rowp(B.z, lr, F, e), g.ldr = F, g.C = rowp(B.dz, lr, F, e), g.ldc = F;
     TRY(run_gemm(S, K_GEMM_DX, g));
-    if (per_slice)
-      TRY(launch(S, K_MISC, 0, nb, [&] { return colsum_acc(dt, n, H, dyl, H, (float*)G.b_fc2, ow, st); }));
     // LayerNorm output gradients: per-slice scratch, or (deferred mode) rows of
     // per-layer arenas kept for the once-per-sequence parameter reductions
     void* du2 = per_slice ? S->sc.du2 : rowp(B.du2, lr, H, e);
@@ -480,28 +483,15 @@ tp_status backward_impl(tp_stage* S, int l, int r, const void* dy, void* dx) {
     g = nn(n, H, F, rowp(B.dz, lr, F, e), F, P.w_fc1);
     g.C = du2, g.ldc = H;
     TRY(run_gemm(S, K_GEMM_DX, g));
-    if (per_slice)
-      TRY(launch(S, K_MISC, 0, (double)n * F * e, [&] {
-        return colsum_acc(dt, n, F, rowp(B.dz, lr, F, e), F, (float*)G.b_fc1, ow, st);
-      }));
     // LN2 backward + residual: dx1 = dy + LN2^T(du2)
     TRY(launch(S, K_NORM, 0, 4 * nb, [&] {
       return ln_bwd(dt, n, H, du2, x1, mx, B.mean2 + lr, B.rstd2 + lr, P.ln2_g,
                     dyl, rowp(B.dx1, lr, H, e), st);
     }));
-    if (per_slice)
-      TRY(launch(S, K_NORM, 0, 2 * nb, [&] {
-        return ln_param_grads(dt, n, H, du2, x1, mx, B.mean2 + lr, B.rstd2 + lr,
-                              (float*)G.ln2_g, (float*)G.ln2_b, ow, st);
-      }));
     // output projection backward: dO = dx1 W_o
     g = nn(n, A, H, rowp(B.dx1, lr, H, e), H, P.w_o);
     g.C = S->sc.dout, g.ldc = A;
     TRY(run_gemm(S, K_GEMM_DX, g));
-    if (per_slice)
-      TRY(launch(S, K_MISC, 0, nb, [&] {
-        return colsum_acc(dt, n, H, rowp(B.dx1, lr, H, e), H, (float*)G.b_o, ow, st);
-      }));
     // attention backward: dq rows, dK/dV into the fp32 buffer for keys [0, r)
     AttnArgs a;
     a.l = l, a.r = r, a.H = A, a.heads = S->heads, a.d = S->d, a.Lmax = S->L;
@@ -527,31 +517,23 @@ tp_status backward_impl(tp_stage* S, int l, int r, const void* dy, void* dx) {
     g = nn(n, H, 3 * A, rowp(B.dqkv, lr, 3 * A, e), 3 * A, P.w_qkv);
     g.C = du, g.ldc = H;
     TRY(run_gemm(S, K_GEMM_DX, g));
-    if (per_slice)
-      TRY(launch(S, K_MISC, 0, 3.0 * n * A * e, [&] {
-        return colsum_acc(dt, n, 3 * A, rowp(B.dqkv, lr, 3 * A, e), 3 * A, (float*)G.b_qkv, ow, st);
-      }));
     // LN1 backward + residual: dx = dx1 + LN1^T(du)
     void* out = li == 0 ? dx : rowp(S->lb[li - 1].dy, lr, H, e);
     TRY(launch(S, K_NORM, 0, 4 * nb, [&] {
       return ln_bwd(dt, n, H, du, xin, mx, B.mean1 + lr, B.rstd1 + lr, P.ln1_g,
                     rowp(B.dx1, lr, H, e), out, st);
     }));
-    if (per_slice)
-      TRY(launch(S, K_NORM, 0, 2 * nb, [&] {
-        return ln_param_grads(dt, n, H, du, xin, mx, B.mean1 + lr, B.rstd1 + lr,
-                              (float*)G.ln1_g, (float*)G.ln1_b, ow, st);
-      }));
     if (per_slice) {
-      tp_status s = wgrad_gemms(S, li, lr, n);
+      tp_status s = param_reductions(S, li, lr, n, du2, du);
+      if (s == TP_OK) s = wgrad_gemms(S, li, lr, n);
       if (s != TP_OK) return s;
     }
   }
   if (!per_slice && l == 0 && !S->profiling) {
     for (int li = NL - 1; li >= 0; --li) {
-      tp_status s = deferred_param_reductions(S, li, S->cached_len * S->bsz);
-      if (s != TP_OK) return s;
-      s = wgrad_gemms(S, li, 0, S->cached_len * S->bsz);
+      const int rows = S->cached_len * S->bsz;
+      tp_status s = param_reductions(S, li, 0, rows, S->lb[li].du2, S->lb[li].du);
+      if (s == TP_OK) s = wgrad_gemms(S, li, 0, rows);
       if (s != TP_OK) return s;
     }
   }

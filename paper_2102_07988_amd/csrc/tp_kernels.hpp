@@ -161,16 +161,31 @@ hipError_t ln_fwd(int dtype, int n, int H, const void* x, int x_f32, void* x_cop
 hipError_t ln_bwd(int dtype, int n, int H, const void* du, const void* x, int x_f32,
                   const float* mean, const float* rstd, const void* g, const void* resid, void* dx,
                   hipStream_t s);
-// dg[i] += sum_t du[t][i] * xhat[t][i];  db[i] += sum_t du[t][i]   (fp32 outputs;
-// with store set, = in place of +=)
-hipError_t ln_param_grads(int dtype, int n, int H, const void* du, const void* x, int x_f32,
-                          const float* mean, const float* rstd, float* dg, float* db, int store,
-                          hipStream_t s);
+// Column sums over `rows` rows, several tensors in one launch.  A job: for column
+// i < cols (a multiple of 8), sum[i] += sum_t a[t * lda + i]; with x set, also
+// xsum[i] += sum_t a[t * lda + i] * (x[t * lda + i] - mean[t]) * rstd[t] (the
+// LayerNorm gain gradient; x fp32 where x_f32).  fp32 outputs; with store set, = in
+// place of +=.  Rows and pointers 16-byte aligned.  part: scratch of part_elems
+// floats for the row chunks' sums.
+struct ColJob {
+  const void* a = nullptr;
+  const void* x = nullptr;
+  const float *mean = nullptr, *rstd = nullptr;
+  float *sum = nullptr, *xsum = nullptr;
+  int cols = 0;
+  long lda = 0;
+  int block0 = 0, slot0 = 0;  // set by the launcher: first block, first partial column
+};
+struct ColJobs {
+  ColJob job[6];
+  int count = 0, rows = 0, store = 0;
+  float* part = nullptr;
+  long part_elems = 0;
+  int rows_per = 0, chunks = 0, slots = 0;  // set by the launcher
+};
+hipError_t col_reduce(int dtype, int x_f32, ColJobs jobs, hipStream_t s);
 // dst[i] = fp16(src[i]) for n bf16 values (round to nearest even).
 hipError_t cvt_bf16_f16(size_t n, const void* src, void* dst, hipStream_t s);
-// out[j] += sum_{i<n} A[i*lda + j], j < N (fp32 output; with store set, = in place of +=)
-hipError_t colsum_acc(int dtype, int n, int N, const void* A, long lda, float* out, int store,
-                      hipStream_t s);
 // dqkv[i][H + j] = dk[l+i][j], dqkv[i][2H + j] = dv[l+i][j] (stage dtype <- fp32)
 hipError_t pack_dkv(int dtype, int n, int H, const float* dk, const float* dv, void* dqkv,
                     hipStream_t s);
