@@ -125,9 +125,8 @@ size_t tp_stage_workspace_bytes(const tp_stage_config *cfg);
  * 256-byte aligned, owned by the caller and used only by this stage until
  * tp_stage_destroy.  stream: a hipStream_t (NULL = default stream) on which
  * all of the stage's device work is enqueued.  Host only: nothing is enqueued.
- * The new stage holds no sequence: its dK/dV buffer holds whatever the
- * workspace held and the fp16 W_qkv copy is not taken, so every slice call
- * returns TP_ERR_ORDER until tp_kv_prefix_reset starts a sequence.
+ * The new stage holds no sequence: the fp16 W_qkv copy is not taken, so every
+ * slice call returns TP_ERR_ORDER until tp_kv_prefix_reset starts a sequence.
  * Errors: TP_ERR_INVALID, TP_ERR_UNSUPPORTED, TP_ERR_WORKSPACE. */
 tp_status tp_stage_init(const tp_stage_config *cfg, const tp_layer_ptrs *params,
                         const tp_layer_ptrs *grads, void *workspace, size_t workspace_bytes,
@@ -137,10 +136,10 @@ tp_status tp_stage_init(const tp_stage_config *cfg, const tp_layer_ptrs *params,
 void tp_stage_destroy(tp_stage *stage);
 
 /* Start a new sequence (required before the first slice call after
- * tp_stage_init or tp_profile_slice_cost): no cached tokens, backward frontier 0, and the fp32
- * dK/dV buffer zeroed (enqueued on the stream; a fill kernel, no memset node);
+ * tp_stage_init or tp_profile_slice_cost): no cached tokens, backward frontier 0;
  * on the mixed-precision path (see Conventions) also the fp16 copy of every
- * layer's W_qkv taken.
+ * layer's W_qkv taken.  (The fp32 dK/dV buffer needs no clearing: the sequence's
+ * first backward slice reaches every cached position and stores its rows.)
  * This is the empty prefix state of Eq. 2: the keys and values of positions
  * before the first slice, which every later slice's attention sums over,
  * start out empty (Sec. 3.2: the cell keeps them from slice to slice).

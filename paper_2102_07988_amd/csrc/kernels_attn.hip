@@ -31,6 +31,8 @@
 #include "tp_kernels.hpp"
 #include "tp_lds.hpp"
 
+#include <algorithm>
+
 namespace tp {
 
 namespace {
@@ -464,41 +466,54 @@ __device__ inline void wait_vm_stores(int k) {
   }
 }
 
-// Adds a wave's 32-key block of fp32 results, acc[j][v] * mul for key
-// s0 + 8 (v / 4) + 4 G + v % 4 and column 32 j + c, into the fp32 buffer buf
-// (this head's first column, rows of H); keys >= r are left out.  When all 32
-// keys exist, the loads of column block j + 1 are issued before block j is
-// added and stored, so the read latency is paid about once.
+// A wave's 32-key block of fp32 results, acc[j][v] * mul for key s0 + 8 (v / 4) +
+// 4 G + v % 4 and column 32 j + c (keys >= r left out), added to the fp32 buffer buf
+// (this head's first column, rows of H) for keys < init and stored for later ones;
+// the sums of keys >= pack_l leave as bf16 rows of `pack` (row key - pack_l, ldp
+// elements apart) instead.  A block of one kind issues the loads of column block
+// j + 1 before block j is added and stored, so the read latency is paid about once.
 template <int JB>
-__device__ inline void add_rows_f32(float* buf, const f32x16_t (&acc)[JB], float mul, int s0,
-                                    int r, int H, int G, int c) {
-  if (s0 + 32 <= r) {
+__device__ inline void out_rows(float* buf, const f32x16_t (&acc)[JB], float mul, int s0, int r,
+                                int H, int G, int c, int init, uint16_t* pack, int pack_l,
+                                long ldp) {
+  auto row = [&](int v) { return 8 * (v >> 2) + 4 * G + (v & 3); };
+  const bool add = s0 + 32 <= init, pk = s0 >= pack_l;
+  if (s0 + 32 <= r && (add || s0 >= init) && (pk || s0 + 32 <= pack_l)) {
     float* b = buf + (long)s0 * H + c;
-    auto rowoff = [&](int v) { return (long)(8 * (v >> 2) + 4 * G + (v & 3)) * H; };
+    uint16_t* q = pk ? pack + (long)(s0 - pack_l) * ldp + c : nullptr;
     float cur[16];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) cur[v] = b[rowoff(v)];
+    for (int v = 0; v < 16; ++v) cur[v] = add ? b[(long)row(v) * H] : 0.f;
 #pragma unroll
     for (int j = 0; j < JB; ++j) {
       float nx[16];
-      if (j + 1 < JB) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) nx[v] = b[rowoff(v) + 32 * (j + 1)];
+      for (int v = 0; v < 16; ++v)
+        nx[v] = add && j + 1 < JB ? b[(long)row(v) * H + 32 * (j + 1)] : 0.f;
+      if (pk) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          q[row(v) * ldp + 32 * j] = f32_to_bf16_bits(cur[v] + acc[j][v] * mul);
+      } else {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) b[(long)row(v) * H + 32 * j] = cur[v] + acc[j][v] * mul;
       }
 #pragma unroll
-      for (int v = 0; v < 16; ++v) b[rowoff(v) + 32 * j] = cur[v] + acc[j][v] * mul;
-      if (j + 1 < JB) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) cur[v] = nx[v];
-      }
+      for (int v = 0; v < 16; ++v) cur[v] = nx[v];
     }
   } else {
 #pragma unroll
     for (int j = 0; j < JB; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int key = s0 + 8 * (v >> 2) + 4 * G + (v & 3);
-        if (key < r) buf[(long)key * H + 32 * j + c] += acc[j][v] * mul;
+        const int key = s0 + row(v);
+        if (key >= r) continue;
+        float* b = buf + (long)key * H + 32 * j + c;
+        const float x = (key < init ? *b : 0.f) + acc[j][v] * mul;
+        if (key >= pack_l)
+          pack[(long)(key - pack_l) * ldp + 32 * j + c] = f32_to_bf16_bits(x);
+        else
+          *b = x;
       }
   }
 }
@@ -523,9 +538,9 @@ __device__ inline void add_rows_f32(float* buf, const f32x16_t (&acc)[JB], float
 // F16: q and k are fp16 (scores on fp16 operands; the dK kernel's dS product
 // on fp16 dS); v and the gradients stay bf16.
 template <int D, int NW, int MODE, int ST, bool F16>
-__global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dkdv_mfma(AttnArgs a0) {
+__device__ inline void dkdv_body(const AttnArgs& a0, int seq) {
   static_assert(MODE >= 1 && MODE <= 3, "dV (1), dK (2), dK storing dS (3)");
-  const AttnArgs a = attn_seq_view<uint16_t>(a0);
+  const AttnArgs a = attn_seq_view<uint16_t>(a0, seq);
   using T = Tile<D>;
   constexpr bool DO_K = MODE >= 2, DO_V = MODE == 1, STORE = MODE == 3;
   constexpr int NTH = 64 * NW, BQ = 32, KS = D / 16, JB = D / 32;
@@ -549,7 +564,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dkdv_mfma(AttnArgs a0) {
   // query-tile ring, and reads them per query block
   constexpr bool V_LDS = DO_K;
   // this lane's row in query block 0 of the stored dS plane (MODE 3)
-  const long prow = STORE ? ((long)blockIdx.z * a.heads + h) * a.r * a.pd_ld + (long)s_me * 32 : 0;
+  const long prow = STORE ? ((long)seq * a.heads + h) * a.r * a.pd_ld + (long)s_me * 32 : 0;
   u32x4 kf[KS];
 #pragma unroll
   for (int kk = 0; kk < KS; ++kk) {
@@ -715,8 +730,27 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dkdv_mfma(AttnArgs a0) {
     }
   }
   // dk[j][v], dv[j][v]: key s_w + 8 (v / 4) + 4 G + v % 4, column 32 j + c
-  if constexpr (DO_K) add_rows_f32<JB>(a.dk + h * D, dk, a.scale, s_w, a.r, H, G, c);
-  if constexpr (DO_V) add_rows_f32<JB>(a.dv + h * D, dv, 1.f, s_w, a.r, H, G, c);
+  uint16_t* pack = (uint16_t*)a.pack + a.H + h * D;
+  if constexpr (DO_K)
+    out_rows<JB>(a.dk + h * D, dk, a.scale, s_w, a.r, H, G, c, a.dkv_init, pack, a.pack_l, a.ld_dq);
+  if constexpr (DO_V)
+    out_rows<JB>(a.dv + h * D, dv, 1.f, s_w, a.r, H, G, c, a.dkv_init, pack + a.H, a.pack_l,
+                 a.ld_dq);
+}
+
+// The dK blocks (MODE MK, ring of STK tiles), then the dV blocks (ring of STV) of
+// every sequence, in one launch: they are independent, and a 256-token slice has
+// too few of either to fill the chip (16 heads, up to 2048 keys: 28 + 17 us one after
+// the other, 31 us together; short prefixes, 4-wave blocks, 30 -> 22 us).  With enough
+// blocks it still saves a part-empty last round (96 heads: 123 -> 114 us; 16 heads and
+// 8k keys: 114 -> 105 us).
+template <int D, int NW, int MK, int STK, int STV, bool F16>
+__global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dkdv_mfma(AttnArgs a) {
+  const int seq = blockIdx.z % a.bs;
+  if ((int)blockIdx.z < a.bs)
+    dkdv_body<D, NW, MK, STK, F16>(a, seq);
+  else
+    dkdv_body<D, NW, 1, STV, F16>(a, seq);
 }
 
 // ------------------------------------------------------------------- dQ
@@ -864,9 +898,12 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dq_mfma(AttnArgs a0) {
 // rows and the stored dS rows of the block's 32-query blocks (128 or 256
 // queries) move through an LDS ring; each wave owns QH blocks of 32 queries.
 // Rows of keys >= r (repeats in the last tile) are zeroed in the dS operand.
-template <int D, int NW, int QH, int ST, bool F16>
+// SPLIT: this block takes only split blockIdx.z % nsplit of the keys and leaves its
+// unscaled fp32 dQ partial.
+template <int D, int NW, int QH, int ST, bool SPLIT, bool F16>
 __global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dq_stream(AttnArgs a0) {
   const AttnArgs a = attn_seq_view<uint16_t>(a0);
+  const int zsp = SPLIT ? blockIdx.z % a.nsplit : 0, seq = blockIdx.z / a.nsplit;
   using TK = Tile<D>;
   constexpr int NTH = 64 * NW, BKV = 64, JB = D / 32, QB = 32 * QH * NW;
   static_assert(QB == 128 || QB == 256, "128 or 256 query columns per block");
@@ -879,7 +916,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dq_stream(AttnArgs a0) {
   const int i_lo = blockIdx.x * QB, q_lo = a.l + i_lo;
   const long qstride = (long)a.r * 32;  // elements between query blocks
   const uint16_t* Sp =
-      a.dst + ((long)blockIdx.z * a.heads + h) * a.r * a.pd_ld + (long)(i_lo >> 5) * qstride;
+      a.dst + ((long)seq * a.heads + h) * a.r * a.pd_ld + (long)(i_lo >> 5) * qstride;
   const uint16_t* Kc = (const uint16_t*)a.kc + h * D;
   const int kend_blk = min(a.r, q_lo + QB);
   const uint32_t sbase = lds_addr(smem);
@@ -888,7 +925,11 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dq_stream(AttnArgs a0) {
   for (int qh = 0; qh < QH; ++qh)
 #pragma unroll
     for (int j = 0; j < JB; ++j) dq[qh][j] = zero16();
-  const int nkb = (kend_blk + BKV - 1) / BKV;
+  int nkb = (kend_blk + BKV - 1) / BKV, kb0 = 0;
+  if constexpr (SPLIT) {
+    kb0 = zsp * (a.kv_chunk / BKV);
+    nkb = min(nkb, kb0 + a.kv_chunk / BKV);
+  }
   const int wq = __builtin_amdgcn_readfirstlane(w);
   const typename TK::template Dma<BKV, NTH> kd(H, wq);
   const DsDma<NTH, NS> sd(qstride, wq);
@@ -898,8 +939,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dq_stream(AttnArgs a0) {
     kd.issue(Kc + (long)kb * BKV * H, H, rv, st);
     sd.issue(Sp + (long)kb * BKV * 32, qstride, rv, st + TILE_K);
   };
-  for (int i = 0; i < ST - 1 && i < nkb; ++i) issue(i, i);
-  for (int kb = 0; kb < nkb; ++kb) {
+  for (int i = kb0; i < kb0 + ST - 1 && i < nkb; ++i) issue(i % ST, i);
+  for (int kb = kb0; kb < nkb; ++kb) {
     if (kb + ST - 1 <= nkb) wait_vm<(ST - 2) * PER_ISSUE>();
     else wait_vm<0>();
     __builtin_amdgcn_s_barrier();
@@ -950,7 +991,16 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dq_stream(AttnArgs a0) {
 #pragma unroll
   for (int qh = 0; qh < QH; ++qh) {
     const int t = q_lo + 32 * (QH * w + qh) + c;
-    if (t < a.r) {
+    if (SPLIT && t < a.r) {
+      float* P = a.ws + (long)zsp * (a.r - a.l) * a.bs * a.H + (long)seq * a.H +
+                 (long)(t - a.l) * H + h * D;
+#pragma unroll
+      for (int j = 0; j < JB; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; v += 4)
+          *(float4*)(P + 32 * j + 8 * (v >> 2) + 4 * G) = make_float4(
+              dq[qh][j][v], dq[qh][j][v + 1], dq[qh][j][v + 2], dq[qh][j][v + 3]);
+    } else if (t < a.r) {
       uint16_t* dQ = (uint16_t*)a.dq + (long)(t - a.l) * a.ld_dq + h * D;
 #pragma unroll
       for (int j = 0; j < JB; ++j)
@@ -1141,22 +1191,57 @@ hipError_t dq_d(const AttnArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Backward with stored dS, after the dV kernel: over query chunks of at most
-// cq rows (a multiple of 256) whose dS planes fit the scratch, the dK kernel
-// (MODE 3) writes the planes that the streaming dQ kernel then reads (the
-// rows' D = rowsum(dO * O) is already computed for the whole slice).
+// Key-range splits of the streaming dQ kernel: its blocks (128 queries of a head) do
+// one short product per key tile, so a launch of few blocks is a long serial chain of
+// tile loads.  Launches of up to 128 blocks split to about two blocks per CU (what
+// their LDS allows), at least 256 keys a split: 16 heads, 512 queries after up to 7680
+// keys, 69 -> 31 us (+ 7 us combine); 256 queries after up to 1792, 25 -> 10 us (+ 5).
+// 192 blocks (96 heads, 256 queries) are faster unsplit: 30 us against 34 + 9.
+void plan_stream_split(AttnArgs& a) {
+  a.nsplit = 1;
+  const int n = a.r - a.l;
+  const long wgs = (long)cdiv(n, 128) * a.heads * a.bs;
+  if (!a.ws || wgs > 128) return;
+  int ns = (int)std::min<long>({MAX_SPLIT, cdiv(512, wgs), cdiv(a.r, 256)});
+  while (ns > 1 && (long)ns * n * a.bs * a.H > a.ws_elems) --ns;
+  if (ns < 2) return;
+  a.kv_chunk = cdiv(cdiv(a.r, ns), 64) * 64;
+  a.nsplit = cdiv(a.r, a.kv_chunk);
+}
+
+template <int D, int NW, int MK, int STK, int STV, bool F16>
+hipError_t launch_dkdv(const AttnArgs& a, hipStream_t s) {
+  constexpr size_t lds_k = STK * (2 * 32 * D + NW * 128) * 2 + 32 * NW * D * 2;
+  constexpr size_t lds_v = STV * (2 * 32 * D + NW * 128) * 2;
+  constexpr size_t lds = lds_k > lds_v ? lds_k : lds_v;
+  hipError_t e = set_lds(attn_bwd_dkdv_mfma<D, NW, MK, STK, STV, F16>, lds);
+  if (e != hipSuccess) return e;
+  attn_bwd_dkdv_mfma<D, NW, MK, STK, STV, F16>
+      <<<dim3(cdiv(a.r, 32 * NW), a.heads, 2 * a.bs), 64 * NW, lds, s>>>(a);
+  return hipGetLastError();
+}
+
+// Block shapes of the dK / dV kernel: with head width 128 8 waves (256 keys) over
+// 4-tile rings (137 KB, the dK blocks' V rows included: one block per CU), with 64 4
+// waves over rings of 2 (dK) and 4 (dV) tiles.
+template <int D, int MK, bool F16>
+hipError_t dkdv_d(const AttnArgs& a, hipStream_t s) {
+  return launch_dkdv<D, D == 128 ? 8 : 4, MK, D == 128 ? 4 : 2, 4, F16>(a, s);
+}
+
+// Backward with stored dS: over query chunks of at most cq rows (a multiple of 256)
+// whose dS planes fit the scratch, the dK blocks (MODE 3) write the planes that the
+// streaming dQ kernel then reads (the rows' D = rowsum(dO * O) is already computed
+// for the whole slice).
 template <int D, bool F16>
 hipError_t bwd_stored(const AttnArgs& a, hipStream_t s, long cq) {
-  constexpr int NWK = D == 128 ? 8 : 4, STK = D == 128 ? 4 : 2;
-  constexpr size_t lds_k = STK * (2 * 32 * D + NWK * 128) * 2 + 32 * NWK * D * 2;
   // dQ: 256 queries per block (8 waves) when that fills the CUs, else 128
   constexpr int STQ = 2;
   constexpr size_t lds_q4 = STQ * (64 * D + 64 * 128) * 2, lds_q8 = STQ * (64 * D + 64 * 256) * 2;
   const bool q8 = (long)cdiv(std::min<long>(a.r - a.l, cq), 256) * a.heads * a.bs >= 128;
-  hipError_t e = set_lds(attn_bwd_dkdv_mfma<D, NWK, 3, STK, F16>, lds_k);
-  if (e == hipSuccess)
-    e = q8 ? set_lds(attn_bwd_dq_stream<D, 8, 1, STQ, F16>, lds_q8)
-           : set_lds(attn_bwd_dq_stream<D, 4, 1, STQ, F16>, lds_q4);
+  hipError_t e = q8 ? set_lds(attn_bwd_dq_stream<D, 8, 1, STQ, false, F16>, lds_q8)
+                    : set_lds(attn_bwd_dq_stream<D, 4, 1, STQ, false, F16>, lds_q4);
+  if (e == hipSuccess) e = set_lds(attn_bwd_dq_stream<D, 4, 1, STQ, true, F16>, lds_q4);
   if (e != hipSuccess) return e;
   const int n = a.r - a.l;
   for (int c0 = 0; c0 < n; c0 += (int)cq) {
@@ -1169,16 +1254,25 @@ hipError_t bwd_stored(const AttnArgs& a, hipStream_t s, long cq) {
     b.dq = (uint16_t*)a.dq + (long)c0 * a.ld_dq;
     b.pd_ld = (long)cdiv(c1 - c0, 256) * 256;  // whole dQ blocks of either width
     b.dst = a.pd;
-    attn_bwd_dkdv_mfma<D, NWK, 3, STK, F16>
-        <<<dim3(cdiv(b.r, 32 * NWK), a.heads, a.bs), 64 * NWK, lds_k, s>>>(b);
-    e = hipGetLastError();
+    // an earlier chunk has left sums for every key it saw; only the last one's are final
+    if (c0 > 0) b.dkv_init = std::max(a.dkv_init, a.l + c0);
+    if (c1 < n) b.pack_l = b.r;
+    e = dkdv_d<D, 3, F16>(b, s);
     if (e != hipSuccess) return e;
-    if (q8)
-      attn_bwd_dq_stream<D, 8, 1, STQ, F16>
+    if (!q8) plan_stream_split(b);
+    if (b.nsplit > 1) {
+      attn_bwd_dq_stream<D, 4, 1, STQ, true, F16>
+          <<<dim3(cdiv(c1 - c0, 128), a.heads, a.bs * b.nsplit), 256, lds_q4, s>>>(b);
+      e = hipGetLastError();
+      if (e != hipSuccess) return e;
+      attn_dq_combine<<<cdiv((long)(c1 - c0) * a.bs * (a.H / 8), 256), 256, 0, s>>>(b);
+    } else if (q8) {
+      attn_bwd_dq_stream<D, 8, 1, STQ, false, F16>
           <<<dim3(cdiv(c1 - c0, 256), a.heads, a.bs), 512, lds_q8, s>>>(b);
-    else
-      attn_bwd_dq_stream<D, 4, 1, STQ, F16>
+    } else {
+      attn_bwd_dq_stream<D, 4, 1, STQ, false, F16>
           <<<dim3(cdiv(c1 - c0, 128), a.heads, a.bs), 256, lds_q4, s>>>(b);
+    }
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -1192,49 +1286,19 @@ hipError_t bwd_d(const AttnArgs& a, hipStream_t s) {
   attn_bwd_rowdot<D><<<dim3(cdiv((long)n * a.heads, 4), 1, a.bs), 256, 0, s>>>(a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // dV kernel: 4 waves, a 4-tile ring (69 KB, two blocks per CU).  dK kernel:
-  // the block's V rows stay in LDS; with head width 128 it runs 8 waves (256
-  // keys) over a 4-tile ring (137 KB, one block per CU), with 64 4 waves over
-  // a 2-tile ring.
-  constexpr int STA = 4;
-  constexpr int NWK = D == 128 ? 8 : 4, STK = D == 128 ? 4 : 2;
-  constexpr size_t lds_a = STA * (2 * 32 * D + NWF * 128) * 2;
-  constexpr size_t lds_k = STK * (2 * 32 * D + NWK * 128) * 2 + 32 * NWK * D * 2;
-  if ((long)cdiv(a.r, 32 * NWF) * a.heads * a.bs < 128) {
-    // few key blocks (few heads, short prefix): two-wave dV blocks and
-    // four-wave dK blocks over two-tile rings, so more blocks share the CUs
-    constexpr size_t lds_v2 = 2 * (2 * 32 * D + 2 * 128) * 2;
-    constexpr size_t lds_k4 = 2 * (2 * 32 * D + 4 * 128) * 2 + 32 * 4 * D * 2;
-    e = set_lds(attn_bwd_dkdv_mfma<D, 2, 1, 2, F16>, lds_v2);
-    if (e != hipSuccess) return e;
-    attn_bwd_dkdv_mfma<D, 2, 1, 2, F16>
-        <<<dim3(cdiv(a.r, 64), a.heads, a.bs), 128, lds_v2, s>>>(a);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    e = set_lds(attn_bwd_dkdv_mfma<D, 4, 2, 2, F16>, lds_k4);
-    if (e != hipSuccess) return e;
-    attn_bwd_dkdv_mfma<D, 4, 2, 2, F16>
-        <<<dim3(cdiv(a.r, 128), a.heads, a.bs), 256, lds_k4, s>>>(a);
-    e = hipGetLastError();
+  if ((long)cdiv(a.r, 128) * a.heads * a.bs < 128) {
+    // few key blocks (few heads, short prefix): four-wave blocks over two-tile
+    // rings, so more blocks share the CUs
+    e = launch_dkdv<D, 4, 2, 2, 2, F16>(a, s);
     if (e != hipSuccess) return e;
     return dq_d<D, F16>(a, s);
   }
-  e = set_lds(attn_bwd_dkdv_mfma<D, NWF, 1, STA, F16>, lds_a);
-  if (e != hipSuccess) return e;
-  attn_bwd_dkdv_mfma<D, NWF, 1, STA, F16>
-      <<<dim3(cdiv(a.r, 32 * NWF), a.heads, a.bs), 64 * NWF, lds_a, s>>>(a);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
   if (a.pd) {
     // query rows per chunk whose dS planes (whole 256-query blocks) fit
     const long cq = a.pd_elems / ((long)a.bs * a.heads * a.r) / 256 * 256;
     if (cq >= 256) return bwd_stored<D, F16>(a, s, cq);
   }
-  e = set_lds(attn_bwd_dkdv_mfma<D, NWK, 2, STK, F16>, lds_k);
-  if (e != hipSuccess) return e;
-  attn_bwd_dkdv_mfma<D, NWK, 2, STK, F16>
-      <<<dim3(cdiv(a.r, 32 * NWK), a.heads, a.bs), 64 * NWK, lds_k, s>>>(a);
-  e = hipGetLastError();
+  e = dkdv_d<D, 2, F16>(a, s);
   if (e != hipSuccess) return e;
   return dq_d<D, F16>(a, s);
 }

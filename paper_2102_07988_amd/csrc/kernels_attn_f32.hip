@@ -340,23 +340,29 @@ __global__ __launch_bounds__(64 * Shape<D>::NW) void attn_dkdv_f32_kernel(AttnAr
     acc_cols<D, false>(dO + (long)i0 * H, H, rows, p, G, c, dv);
     acc_cols<D, false>(Q + (long)i0 * H, H, rows, ds, G, c, dk);
   }
-  // dk[j][v], dv[j][v]: key k_lo + acc_row(v), column 32 j + c; added to the fp32
-  // buffers, each element by one thread
-  auto add = [&](const f32x16_t(&acc)[JB], float* buf, float mul) {
+  // dk[j][v], dv[j][v]: key k_lo + acc_row(v), column 32 j + c; each element of the
+  // fp32 buffers (or, once final, of the dqkv rows) belongs to one thread
+  auto add = [&](const f32x16_t(&acc)[JB], float* buf, float mul, int third) {
     put_cols<D>(sm, w, G, c, acc);
     __syncthreads();
     for (int e = threadIdx.x; e < 32 * D; e += NTH) {
-      const int row = e / D, col = e % D;
-      if (k_lo + row >= a.r) continue;
-      float s = 0.f;
+      const int row = e / D, col = e % D, s = k_lo + row;
+      if (s >= a.r) continue;
+      float x = 0.f;
 #pragma unroll
-      for (int x = 0; x < NW; ++x) s += *part_at<D>(sm, x, row, col);
-      buf[(long)(k_lo + row) * H + h * D + col] += s * mul;
+      for (int z = 0; z < NW; ++z) x += *part_at<D>(sm, z, row, col);
+      x *= mul;
+      float* dst = buf + (long)s * H + h * D + col;
+      if (s < a.dkv_init) x += *dst;
+      if (s >= a.pack_l)
+        st((T*)a.pack + (long)(s - a.pack_l) * a.ld_dq + third * a.H + h * D + col, x);
+      else
+        *dst = x;
     }
     __syncthreads();
   };
-  add(dk, a.dk, a.scale);
-  add(dv, a.dv, 1.f);
+  add(dk, a.dk, a.scale, 1);
+  add(dv, a.dv, 1.f, 2);
 }
 
 template <typename K>

@@ -205,7 +205,8 @@ __device__ inline float2 block_sum2(float a, float b, float* red /* >= 32 floats
 template <typename T, typename TX, int CPT>
 __global__ __launch_bounds__(1024) void ln_bwd_kernel(int H, const T* du, const TX* x,
                                                       const float* mean, const float* rstd,
-                                                      const T* g, const T* resid, T* dx) {
+                                                      const T* g, const T* resid, T* resid_copy,
+                                                      T* dx) {
   __shared__ float red[32];
   const int row = blockIdx.x, nc = H >> 3, nt = blockDim.x;
   const float mu = mean[row], rs = rstd[row];
@@ -218,7 +219,7 @@ __global__ __launch_bounds__(1024) void ln_bwd_kernel(int H, const T* du, const 
       load8(x + (long)row * H + ci * 8, xh[c]);
       load8(du + (long)row * H + ci * 8, dg[c]);
       load8(g + ci * 8, gg);
-      if (resid) load8(resid + (long)row * H + ci * 8, r[c]);
+      load8(resid + (long)row * H + ci * 8, r[c]);
 #pragma unroll
       for (int e = 0; e < 8; ++e) dg[c][e] *= gg[e];
     }
@@ -242,8 +243,9 @@ __global__ __launch_bounds__(1024) void ln_bwd_kernel(int H, const T* du, const 
       float o[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e)
-        o[e] = rs * (dg[c][e] - a - xh[c][e] * bm) + (resid ? r[c][e] : 0.f);
+        o[e] = rs * (dg[c][e] - a - xh[c][e] * bm) + r[c][e];
       store8(dx + (long)row * H + ci * 8, o);
+      if (resid_copy) store8(resid_copy + (long)row * H + ci * 8, r[c]);
     }
   }
 }
@@ -348,32 +350,10 @@ __global__ __launch_bounds__(256) void col_finish_kernel(ColJobs J) {
   *out = J.store ? s : *out + s;
 }
 
-// dK and dV (fp32, [n, H]) into the K and V thirds of the dQKV rows, 8
-// consecutive columns per thread (H % 8 == 0; 16-byte aligned pointers).
-template <typename T>
-__global__ void pack_dkv_kernel(int n, int H, const float* dk, const float* dv, T* dqkv) {
-  const int h8 = H >> 3;
-  const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= (long)n * h8) return;
-  const long i = e / h8, j = (e - i * h8) * 8;
-  float v[8];
-  load8(dk + i * H + j, v);
-  store8(dqkv + i * 3 * H + H + j, v);
-  load8(dv + i * H + j, v);
-  store8(dqkv + i * 3 * H + 2 * H + j, v);
-}
-
 __global__ void fill_f32_kernel(float* p, size_t n, float v) {
   for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
        e += (size_t)gridDim.x * blockDim.x)
     p[e] = v;
-}
-
-template <typename T>
-__global__ void copy_kernel(size_t n, const T* src, T* dst) {
-  for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
-       e += (size_t)gridDim.x * blockDim.x)
-    dst[e] = src[e];
 }
 
 hipError_t ln_fwd(int dtype, int n, int H, const void* x, int x_f32, void* x_copy, int copy_f32,
@@ -398,14 +378,15 @@ hipError_t ln_fwd(int dtype, int n, int H, const void* x, int x_f32, void* x_cop
 }
 
 hipError_t ln_bwd(int dtype, int n, int H, const void* du, const void* x, int x_f32,
-                  const float* mean, const float* rstd, const void* g, const void* resid, void* dx,
-                  hipStream_t s) {
+                  const float* mean, const float* rstd, const void* g, const void* resid,
+                  void* resid_copy, void* dx, hipStream_t s) {
   clear_stale_error();
   if (n <= 0) return hipSuccess;
   const LnShape sh = ln_shape(H);
 #define TP_LN(TT, TX, C)                                                                   \
   ln_bwd_kernel<TT, TX, C><<<n, sh.nt, 0, s>>>(H, (const TT*)du, (const TX*)x, mean, rstd,  \
-                                               (const TT*)g, (const TT*)resid, (TT*)dx)
+                                               (const TT*)g, (const TT*)resid,              \
+                                               (TT*)resid_copy, (TT*)dx)
   if (dtype == DT_FP32) {
     if (sh.cpt == 1) TP_LN(float, float, 1); else TP_LN(float, float, 2);
   } else if (x_f32) {
@@ -485,37 +466,11 @@ hipError_t cvt_bf16_f16(size_t n, const void* src, void* dst, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t pack_dkv(int dtype, int n, int H, const float* dk, const float* dv, void* dqkv,
-                    hipStream_t s) {
-  clear_stale_error();
-  const long tot = (long)n * (H / 8);
-  if (tot <= 0) return hipSuccess;
-  auto al = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
-  if (H % 8 || !al(dk) || !al(dv) || !al(dqkv)) return hipErrorInvalidValue;
-  if (dtype == DT_FP32)
-    pack_dkv_kernel<float><<<cdiv(tot, 256), 256, 0, s>>>(n, H, dk, dv, (float*)dqkv);
-  else
-    pack_dkv_kernel<bf16><<<cdiv(tot, 256), 256, 0, s>>>(n, H, dk, dv, (bf16*)dqkv);
-  return hipGetLastError();
-}
-
 hipError_t fill_f32(float* p, size_t n, float v, hipStream_t s) {
   clear_stale_error();
   if (n == 0) return hipSuccess;
   const int blocks = (int)((n + 255) / 256 < 8192 ? (n + 255) / 256 : 8192);
   fill_f32_kernel<<<blocks, 256, 0, s>>>(p, n, v);
-  return hipGetLastError();
-}
-
-hipError_t copy_rows(int dtype, int n, int H, const void* src, void* dst, hipStream_t s) {
-  clear_stale_error();
-  const size_t tot = (size_t)n * H;
-  if (tot == 0) return hipSuccess;
-  const int blocks = (int)((tot + 255) / 256 < 8192 ? (tot + 255) / 256 : 8192);
-  if (dtype == DT_FP32)
-    copy_kernel<float><<<blocks, 256, 0, s>>>(tot, (const float*)src, (float*)dst);
-  else
-    copy_kernel<bf16><<<blocks, 256, 0, s>>>(tot, (const bf16*)src, (bf16*)dst);
   return hipGetLastError();
 }
 

@@ -89,7 +89,7 @@ struct tp_stage {
   hipStream_t stream;
   int cached_len = 0, bwd_frontier = 0;
   // a sequence has been started by tp_kv_prefix_reset since the stage was
-  // created or last profiled (the dK/dV buffer is zero, the fp16 W_qkv copy taken)
+  // created or last profiled (the fp16 W_qkv copy is taken)
   bool prepared = false;
   // the sequence's next gradient writes store rather than add
   // (TP_SEQ_OVERWRITE_GRADS; cleared once every gradient has been written)
@@ -463,16 +463,19 @@ tp_status backward_impl(tp_stage* S, int l, int r, const void* dy, void* dx) {
   const bool per_slice = S->cfg.wgrad_mode == TP_WGRAD_PER_SLICE;
   const double nb = (double)n * H * e;
   const bool mx = S->mixed;
+  const bool first = !S->profiling && r == S->cached_len;
   for (int li = NL - 1; li >= 0; --li) {
     LayerBufs& B = S->lb[li];
     const tp_layer_ptrs& P = S->P[li];
     void* dyl = rowp(B.dy, lr, H, e);
     const void* x1 = rowp(B.x1, lr, H, S->resz);
     const void* xin = rowp(B.x_in, lr, H, S->resz);
-    if (li == NL - 1)
-      TRY(launch(S, K_MISC, 0, 2 * nb, [&] { return copy_rows(dt, n, H, dy, dyl, st); }));
+    // the last layer reads the caller's dy rows; LN2's backward copies them to the
+    // arena for the weight gradients
+    const bool last = li == NL - 1;
+    const void* dyr = last ? dy : dyl;
     // FC2 backward (dX fused with GELU'): dz = (dy W2) * GELU'(z)
-    GemmArgs g = nn(n, F, H, dyl, H, P.w_fc2);
+    GemmArgs g = nn(n, F, H, dyr, H, P.w_fc2);
     g.epi = EPI_DGELU, g.R = rowp(B.z, lr, F, e), g.ldr = F, g.C = rowp(B.dz, lr, F, e), g.ldc = F;
     TRY(run_gemm(S, K_GEMM_DX, g));
     // LayerNorm output gradients: per-slice scratch, or (deferred mode) rows of
@@ -486,7 +489,7 @@ tp_status backward_impl(tp_stage* S, int l, int r, const void* dy, void* dx) {
     // LN2 backward + residual: dx1 = dy + LN2^T(du2)
     TRY(launch(S, K_NORM, 0, 4 * nb, [&] {
       return ln_bwd(dt, n, H, du2, x1, mx, B.mean2 + lr, B.rstd2 + lr, P.ln2_g,
-                    dyl, rowp(B.dx1, lr, H, e), st);
+                    dyr, last ? dyl : nullptr, rowp(B.dx1, lr, H, e), st);
     }));
     // output projection backward: dO = dx1 W_o
     g = nn(n, A, H, rowp(B.dx1, lr, H, e), H, P.w_o);
@@ -505,14 +508,14 @@ tp_status backward_impl(tp_stage* S, int l, int r, const void* dy, void* dx) {
     a.dout = S->sc.dout, a.D = S->sc.D;
     a.dq = rowp(B.dqkv, lr, 3 * A, e), a.ld_dq = (long)S->bsz * 3 * A, a.dq_seq = 3 * A;
     a.dk = B.dk, a.dv = B.dv;
+    // the sequence's first backward slice finds no sums in the buffers; the slice's
+    // own keys see no later backward slice
+    a.dkv_init = first ? 0 : r;
+    a.pack_l = l, a.pack = a.dq;
     const double pairs = ((double)ntok * l + (double)ntok * (ntok + 1) / 2) * S->bsz;
     TRY(launch(S, K_ATTN_BWD, 8.0 * A * pairs,
                ((4.0 * ntok + 2.0 * r) * A * e + 16.0 * r * A) * S->bsz,
                [&] { return attn_bwd(dt, a, st); }));
-    TRY(launch(S, K_MISC, 0, (8.0 + 4.0 * e) * n * A, [&] {
-      return pack_dkv(dt, n, A, B.dk + (long)lr * A, B.dv + (long)lr * A,
-                      rowp(B.dqkv, lr, 3 * A, e), st);
-    }));
     // QKV backward: du = [dq dk dv] W_qkv
     g = nn(n, H, 3 * A, rowp(B.dqkv, lr, 3 * A, e), 3 * A, P.w_qkv);
     g.C = du, g.ldc = H;
@@ -521,7 +524,7 @@ tp_status backward_impl(tp_stage* S, int l, int r, const void* dy, void* dx) {
     void* out = li == 0 ? dx : rowp(S->lb[li - 1].dy, lr, H, e);
     TRY(launch(S, K_NORM, 0, 4 * nb, [&] {
       return ln_bwd(dt, n, H, du, xin, mx, B.mean1 + lr, B.rstd1 + lr, P.ln1_g,
-                    rowp(B.dx1, lr, H, e), out, st);
+                    rowp(B.dx1, lr, H, e), nullptr, out, st);
     }));
     if (per_slice) {
       tp_status s = param_reductions(S, li, lr, n, du2, du);
@@ -604,11 +607,6 @@ tp_status tp_kv_prefix_reset(tp_stage* S) { return tp_kv_prefix_reset_ex(S, 0); 
 
 tp_status tp_kv_prefix_reset_ex(tp_stage* S, unsigned flags) {
   if (!S || (flags & ~(TP_SEQ_OVERWRITE_GRADS | TP_SEQ_REUSE_WQKV_COPY))) return TP_ERR_INVALID;
-  const size_t n = (size_t)S->L * S->bsz * S->A;
-  for (auto& B : S->lb) {
-    TRY(fill_f32(B.dk, n, 0.f, S->stream));
-    TRY(fill_f32(B.dv, n, 0.f, S->stream));
-  }
   if (!(flags & TP_SEQ_REUSE_WQKV_COPY) || !S->w16_valid) TRY(snapshot_wqkv(S));
   S->cached_len = 0;
   S->bwd_frontier = 0;

@@ -100,6 +100,13 @@ struct AttnArgs {
   long ld_dq = 0, dq_seq = 0;
   float* dk = nullptr;  // fp32 accumulation buffers (absolute rows)
   float* dv = nullptr;
+  // Rows of keys < dkv_init hold sums to add to; later keys' rows are stored
+  // without being read (the sequence's first backward slice reaches every key).
+  // Keys >= pack_l get their last contribution in this call: their dK and dV leave
+  // as stage-dtype rows of dqkv (row key - pack_l of `pack`, ld_dq elements apart,
+  // columns H + .. and 2 H + ..) in place of the fp32 rows.
+  int dkv_init = 0, pack_l = 0;
+  void* pack = nullptr;
   // Key-range split of the query-parallel kernels (forward, dQ) when their
   // grid is small: blockIdx.z = sequence * nsplit + split, split z takes keys
   // [z * kv_chunk, (z + 1) * kv_chunk), and writes fp32 partials that a
@@ -131,8 +138,7 @@ struct AttnArgs {
 // pointers moved to its columns (element type T) and planes; the row stride
 // stays a.ld.
 template <typename T>
-__device__ inline AttnArgs attn_seq_view(AttnArgs a) {
-  const int s = blockIdx.z / a.nsplit;
+__device__ inline AttnArgs attn_seq_view(AttnArgs a, int s) {
   if (s == 0) return a;
   const long off = (long)s * a.H, plane = (long)s * a.heads * a.Lmax;
   a.q = (const T*)a.q + off;
@@ -141,11 +147,16 @@ __device__ inline AttnArgs attn_seq_view(AttnArgs a) {
   if (a.o) a.o = (T*)a.o + off;
   if (a.dout) a.dout = (const T*)a.dout + off;
   if (a.dq) a.dq = (T*)a.dq + s * a.dq_seq;
+  if (a.pack) a.pack = (T*)a.pack + s * a.dq_seq;
   if (a.dk) a.dk += off;
   if (a.dv) a.dv += off;
   if (a.lse) a.lse += plane;
   if (a.D) a.D += plane;
   return a;
+}
+template <typename T>
+__device__ inline AttnArgs attn_seq_view(AttnArgs a) {
+  return attn_seq_view<T>(a, blockIdx.z / a.nsplit);
 }
 hipError_t attn_fwd(int dtype, const AttnArgs& a, hipStream_t s);
 hipError_t attn_bwd(int dtype, const AttnArgs& a, hipStream_t s);
@@ -157,10 +168,11 @@ hipError_t attn_bwd(int dtype, const AttnArgs& a, hipStream_t s);
 hipError_t ln_fwd(int dtype, int n, int H, const void* x, int x_f32, void* x_copy, int copy_f32,
                   const void* g, const void* b, void* u, void* u16, float* mean, float* rstd,
                   float eps, hipStream_t s);
-// dx = LN^T(du) + resid (resid may be null); x fp32 when x_f32.
+// dx = LN^T(du) + resid; x fp32 when x_f32.  If resid_copy is not null, the resid
+// rows are also copied there.
 hipError_t ln_bwd(int dtype, int n, int H, const void* du, const void* x, int x_f32,
-                  const float* mean, const float* rstd, const void* g, const void* resid, void* dx,
-                  hipStream_t s);
+                  const float* mean, const float* rstd, const void* g, const void* resid,
+                  void* resid_copy, void* dx, hipStream_t s);
 // Column sums over `rows` rows, several tensors in one launch.  A job: for column
 // i < cols (a multiple of 8), sum[i] += sum_t a[t * lda + i]; with x set, also
 // xsum[i] += sum_t a[t * lda + i] * (x[t * lda + i] - mean[t]) * rstd[t] (the
@@ -186,10 +198,6 @@ struct ColJobs {
 hipError_t col_reduce(int dtype, int x_f32, ColJobs jobs, hipStream_t s);
 // dst[i] = fp16(src[i]) for n bf16 values (round to nearest even).
 hipError_t cvt_bf16_f16(size_t n, const void* src, void* dst, hipStream_t s);
-// dqkv[i][H + j] = dk[l+i][j], dqkv[i][2H + j] = dv[l+i][j] (stage dtype <- fp32)
-hipError_t pack_dkv(int dtype, int n, int H, const float* dk, const float* dv, void* dqkv,
-                    hipStream_t s);
 hipError_t fill_f32(float* p, size_t n, float v, hipStream_t s);
-hipError_t copy_rows(int dtype, int n, int H, const void* src, void* dst, hipStream_t s);
 
 }  // namespace tp
