@@ -292,6 +292,27 @@ hipError_t run_gemm(tp_stage* S, int cls, GemmArgs g) {
                 [&] { return gemm(S->dt, g, S->stream); });
 }
 
+// The product g, then the LayerNorm nm over its output rows (FWD; BWD: the product is
+// the LayerNorm's output gradient): in the product's split reduction where there is
+// one, else as a launch of its own.
+hipError_t run_gemm_norm(tp_stage* S, int cls, GemmArgs g, const RowNorm& nm) {
+  bool done = false;
+  g.norm = &nm, g.norm_done = &done;
+  const hipError_t e = run_gemm(S, cls, g);
+  if (e != hipSuccess || done) return e;
+  const int H = S->H, n = g.M;
+  const double nb = (double)n * H * S->esz;
+  if (nm.bwd)
+    return launch(S, K_NORM, 0, 4 * nb, [&] {
+      return ln_bwd(S->dt, n, H, g.C, nm.x, nm.x_f32, nm.mean, nm.rstd, nm.g, nm.resid,
+                    nm.resid_copy, nm.dx, S->stream);
+    });
+  return launch(S, K_NORM, 0, 2 * nb, [&] {
+    return ln_fwd(S->dt, n, H, g.C, S->mixed, nullptr, 0, nm.g, nm.b, nm.u, nm.u16, nm.mean,
+                  nm.rstd, nm.eps, S->stream);
+  });
+}
+
 // A(m,k) row-major [M][K] times weight W [N][K] (B(k,n) = W[n][k]).
 GemmArgs nt(int M, int N, int K, const void* A, long lda, const void* W) {
   GemmArgs g;
@@ -404,11 +425,13 @@ tp_status forward_impl(tp_stage* S, int l, int r, const void* x, void* y) {
     const size_t re = S->resz;
     void* xin = rowp(B.x_in, lr, H, re);
     void* x1 = rowp(B.x1, lr, H, re);
-    TRY(launch(S, K_NORM, 0, 2 * nb, [&] {
-      return ln_fwd(dt, n, H, li == 0 ? x : xin, li > 0 && mx, li == 0 ? xin : nullptr, mx,
-                    P.ln1_g, P.ln1_b, rowp(B.u, lr, H, e), mx ? rowp(B.u16, lr, H, 2) : nullptr,
-                    B.mean1 + lr, B.rstd1 + lr, S->cfg.ln_eps, st);
-    }));
+    // later layers' LN1 runs with the previous layer's FC2 product
+    if (li == 0)
+      TRY(launch(S, K_NORM, 0, 2 * nb, [&] {
+        return ln_fwd(dt, n, H, x, 0, xin, mx, P.ln1_g, P.ln1_b, rowp(B.u, lr, H, e),
+                      mx ? rowp(B.u16, lr, H, 2) : nullptr, B.mean1 + lr, B.rstd1 + lr,
+                      S->cfg.ln_eps, st);
+      }));
     GemmArgs g = mx ? nt(n, 3 * A, H, rowp(B.u16, lr, H, 2), H, B.w16)
                     : nt(n, 3 * A, H, rowp(B.u, lr, H, e), H, P.w_qkv);
     g.epi = EPI_QKV;
@@ -436,11 +459,10 @@ tp_status forward_impl(tp_stage* S, int l, int r, const void* x, void* y) {
     g = nt(n, H, A, rowp(B.o, lr, A, e), A, P.w_o);
     g.epi = EPI_RESID, g.bias = P.b_o, g.R = xin, g.ldr = H, g.C = x1, g.ldc = H;
     g.r_f32 = g.c_f32 = mx;
-    TRY(run_gemm(S, K_GEMM_FWD, g));
-    TRY(launch(S, K_NORM, 0, 2 * nb, [&] {
-      return ln_fwd(dt, n, H, x1, mx, nullptr, 0, P.ln2_g, P.ln2_b, rowp(B.u2, lr, H, e), nullptr,
-                    B.mean2 + lr, B.rstd2 + lr, S->cfg.ln_eps, st);
-    }));
+    RowNorm nm;
+    nm.g = P.ln2_g, nm.b = P.ln2_b, nm.u = rowp(B.u2, lr, H, e);
+    nm.mean = B.mean2 + lr, nm.rstd = B.rstd2 + lr, nm.eps = S->cfg.ln_eps;
+    TRY(run_gemm_norm(S, K_GEMM_FWD, g, nm));
     g = nt(n, F, H, rowp(B.u2, lr, H, e), H, P.w_fc1);
     g.epi = EPI_GELU, g.bias = P.b_fc1, g.C = rowp(B.z, lr, F, e), g.ldc = F;
     g.C2 = rowp(B.g, lr, F, e), g.ldc2 = F;
@@ -449,7 +471,16 @@ tp_status forward_impl(tp_stage* S, int l, int r, const void* x, void* y) {
     g.epi = EPI_RESID, g.bias = P.b_fc2, g.R = x1, g.ldr = H, g.r_f32 = mx;
     g.C = li == NL - 1 ? y : rowp(S->lb[li + 1].x_in, lr, H, re), g.ldc = H;
     g.c_f32 = mx && li < NL - 1;
-    TRY(run_gemm(S, K_GEMM_FWD, g));
+    if (li == NL - 1) {
+      TRY(run_gemm(S, K_GEMM_FWD, g));
+    } else {
+      LayerBufs& Bn = S->lb[li + 1];
+      const tp_layer_ptrs& Pn = S->P[li + 1];
+      nm.g = Pn.ln1_g, nm.b = Pn.ln1_b, nm.u = rowp(Bn.u, lr, H, e);
+      nm.u16 = mx ? rowp(Bn.u16, lr, H, 2) : nullptr;
+      nm.mean = Bn.mean1 + lr, nm.rstd = Bn.rstd1 + lr;
+      TRY(run_gemm_norm(S, K_GEMM_FWD, g, nm));
+    }
   }
   return TP_OK;
 }
@@ -485,12 +516,12 @@ tp_status backward_impl(tp_stage* S, int l, int r, const void* dy, void* dx) {
     // FC1 backward: du2 = dz W1
     g = nn(n, H, F, rowp(B.dz, lr, F, e), F, P.w_fc1);
     g.C = du2, g.ldc = H;
-    TRY(run_gemm(S, K_GEMM_DX, g));
-    // LN2 backward + residual: dx1 = dy + LN2^T(du2)
-    TRY(launch(S, K_NORM, 0, 4 * nb, [&] {
-      return ln_bwd(dt, n, H, du2, x1, mx, B.mean2 + lr, B.rstd2 + lr, P.ln2_g,
-                    dyr, last ? dyl : nullptr, rowp(B.dx1, lr, H, e), st);
-    }));
+    // with LN2 backward + residual: dx1 = dy + LN2^T(du2)
+    RowNorm nm;
+    nm.bwd = true, nm.g = P.ln2_g, nm.b = P.ln2_b, nm.x = x1, nm.x_f32 = mx;
+    nm.mean = B.mean2 + lr, nm.rstd = B.rstd2 + lr;
+    nm.resid = dyr, nm.resid_copy = last ? dyl : nullptr, nm.dx = rowp(B.dx1, lr, H, e);
+    TRY(run_gemm_norm(S, K_GEMM_DX, g, nm));
     // output projection backward: dO = dx1 W_o
     g = nn(n, A, H, rowp(B.dx1, lr, H, e), H, P.w_o);
     g.C = S->sc.dout, g.ldc = A;
@@ -519,13 +550,12 @@ tp_status backward_impl(tp_stage* S, int l, int r, const void* dy, void* dx) {
     // QKV backward: du = [dq dk dv] W_qkv
     g = nn(n, H, 3 * A, rowp(B.dqkv, lr, 3 * A, e), 3 * A, P.w_qkv);
     g.C = du, g.ldc = H;
-    TRY(run_gemm(S, K_GEMM_DX, g));
-    // LN1 backward + residual: dx = dx1 + LN1^T(du)
-    void* out = li == 0 ? dx : rowp(S->lb[li - 1].dy, lr, H, e);
-    TRY(launch(S, K_NORM, 0, 4 * nb, [&] {
-      return ln_bwd(dt, n, H, du, xin, mx, B.mean1 + lr, B.rstd1 + lr, P.ln1_g,
-                    rowp(B.dx1, lr, H, e), nullptr, out, st);
-    }));
+    // with LN1 backward + residual: dx = dx1 + LN1^T(du)
+    nm.g = P.ln1_g, nm.b = P.ln1_b, nm.x = xin;
+    nm.mean = B.mean1 + lr, nm.rstd = B.rstd1 + lr;
+    nm.resid = rowp(B.dx1, lr, H, e), nm.resid_copy = nullptr;
+    nm.dx = li == 0 ? dx : rowp(S->lb[li - 1].dy, lr, H, e);
+    TRY(run_gemm_norm(S, K_GEMM_DX, g, nm));
     if (per_slice) {
       tp_status s = param_reductions(S, li, lr, n, du2, du);
       if (s == TP_OK) s = wgrad_gemms(S, li, lr, n);

@@ -22,6 +22,24 @@ enum EpiKind {
                   // GemmArgs::overwrite, Cf[m][n] = acc without the read)
 };
 
+// LayerNorm over the rows a product has just formed (H = N columns), for products
+// whose split partial sums are reduced anyway: the reduction then runs one block per
+// row and goes on with the LayerNorm, instead of a second launch that reads the rows
+// back.  FWD: the product's output rows (EPI_RESID) are normalised (arguments as
+// ln_fwd).  BWD: the product's output rows (EPI_STORE) are the LayerNorm output
+// gradient du (arguments as ln_bwd; resid rows as in ln_bwd).
+struct RowNorm {
+  bool bwd = false;
+  const void *g = nullptr, *b = nullptr;
+  void *u = nullptr, *u16 = nullptr;  // FWD outputs
+  float *mean = nullptr, *rstd = nullptr;  // FWD: written; BWD: read
+  float eps = 0.f;
+  const void* x = nullptr;  // BWD: the LayerNorm's input rows, fp32 when x_f32
+  int x_f32 = 0;
+  const void* resid = nullptr;
+  void *resid_copy = nullptr, *dx = nullptr;
+};
+
 struct GemmArgs {
   int M = 0, N = 0, K = 0;
   const void* A = nullptr;  // A(m,k) = A[m*sam + k*sak]
@@ -50,6 +68,10 @@ struct GemmArgs {
   // EPI_ACC_F32 only: store acc instead of adding it (the destination's old
   // contents are never read)
   int overwrite = 0;
+  // LayerNorm to run on the output rows by a launcher that reduces split partial
+  // sums; *norm_done tells whether it has (else the caller launches it)
+  const RowNorm* norm = nullptr;
+  bool* norm_done = nullptr;
   // fp32 scratch for split-K partial sums (may be null: no split)
   float* ws = nullptr;
   long ws_elems = 0;
