@@ -212,18 +212,41 @@ constexpr int WALK_PER_XCD = 32;
 
 struct TileWalk {
   static constexpr int SM = 4, SN = 8;
-  int tm, tn, stm, stn;
-  __device__ TileWalk(int tiles_m, int tiles_n)
-      : tm(tiles_m), tn(tiles_n), stm((tiles_m + SM - 1) / SM), stn((tiles_n + SN - 1) / SN) {}
-  // output tile of workgroup (xcd, slot) in round r; -1 if that slot is idle
-  __device__ int tile(int r, int xcd, int slot) const {
-    const int s = r * 8 + xcd;
-    if (s >= stm * stn) return -1;
-    const int im = (s / stn) * SM + slot / SN, in = (s % stn) * SN + slot % SN;
+  int tm, tn, stm, stn, sm, sn;
+  // a super-tile is 4 x 8 tiles, or 8 x 4 where `turn` is set
+  __host__ __device__ TileWalk(int tiles_m, int tiles_n, bool turn = false)
+      : tm(tiles_m), tn(tiles_n), sm(turn ? SN : SM), sn(turn ? SM : SN) {
+    stm = (tm + sm - 1) / sm, stn = (tn + sn - 1) / sn;
+  }
+  __host__ __device__ int supers() const { return stm * stn; }
+  // output tile of slot `slot` of super-tile s; -1 if that slot is idle
+  __device__ int tile_of(int s, int slot) const {
+    if (s >= supers()) return -1;
+    const int im = (s / stn) * sm + slot / sn, in = (s % stn) * sn + slot % sn;
     if (im >= tm || in >= tn) return -1;
     return im * tn + in;
   }
+  // output tile of workgroup (xcd, slot) in round r
+  __device__ int tile(int r, int xcd, int slot) const { return tile_of(r * 8 + xcd, slot); }
 };
+
+// Up to four weight-gradient products over the same tokens in one launch: the
+// products of a layer differ in width, and each alone leaves a part-empty last round
+// of workgroups (or, when narrow, most CUs idle).  first[p]: the first workgroup of
+// product p in grid order, or its first super-tile (walk).
+struct GemmGroup {
+  GemmArgs g[4];
+  int first[5];
+  int count, walk;
+};
+// the product of this workgroup (uniform) and its index within it
+__device__ inline const GemmArgs& my_product(const GemmArgs& a, int, int*) { return a; }
+__device__ inline const GemmArgs& my_product(const GemmGroup& a, int i, int* local) {
+  int p = 0;
+  while (p + 1 < a.count && i >= a.first[p + 1]) ++p;
+  *local = i - a.first[p];
+  return a.g[p];
+}
 
 // STAGES k-tiles of A and SB of B are buffered.  SB == STAGES: one ring of
 // (A, B) stages.  SB == STAGES + 1 == 3 ("B leads"): separate rings, the B
@@ -233,8 +256,9 @@ struct TileWalk {
 // otherwise bf16.  TAIL: K need not be whole k-tiles; the values of the last tile
 // past K are zeroed in LDS, in both operands, between two barriers.
 template <int BM, int BN, int BK, int WGM, int WGN, bool A_KC, bool B_KC, int EPI, bool SPLIT,
-          int STAGES, int SB, bool F16, bool TAIL>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_dma_kernel(GemmArgs a) {
+          int STAGES, int SB, bool F16, bool TAIL, typename ARGS>
+__global__ __launch_bounds__(64 * WGM * WGN) void gemm_dma_kernel(ARGS args) {
+  constexpr bool GROUP = std::is_same<ARGS, GemmGroup>::value;
   constexpr int NTH = 64 * WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN, FM = WM / 32, FN = WN / 32;
   constexpr int TILE_A = BM * BK, TILE_B = BN * BK, STAGE = TILE_A + TILE_B;  // elements
@@ -255,6 +279,15 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_dma_kernel(GemmArgs a) {
   static_assert(PATCH <= (BLEAD ? STAGES * TILE_A : STAGES * STAGE), "epilogue patch exceeds LDS");
   extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
 
+  int local = 0;  // GROUP: tile or super-tile within this workgroup's product
+  int gi = blockIdx.x;
+  if constexpr (GROUP) {
+    if (args.walk) {
+      gi = (blockIdx.x / 8 / WALK_PER_XCD) * 8 + blockIdx.x % 8;
+      if (gi >= args.first[args.count]) return;  // uniform per workgroup
+    }
+  }
+  const GemmArgs& a = my_product(args, gi, &local);
   const uint16_t* A = (const uint16_t*)a.A;
   const uint16_t* B = (const uint16_t*)a.B;
   const long lda = A_KC ? a.sam : a.sak;
@@ -268,7 +301,14 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_dma_kernel(GemmArgs a) {
   const uint32_t sbase = lds_addr(smem);
 
   int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  if (!SPLIT && a.walk) {
+  if constexpr (GROUP) {
+    const TileWalk walk(cdiv(a.M, BM), cdiv(a.N, BN), a.walk == 2);
+    const int tile =
+        args.walk ? walk.tile_of(local, blockIdx.x / 8 % WALK_PER_XCD) : local;
+    if (tile < 0) return;  // uniform per workgroup
+    m0 = (tile / walk.tn) * BM;
+    n0 = (tile % walk.tn) * BN;
+  } else if (!SPLIT && a.walk) {
     const TileWalk walk(cdiv(a.M, BM), cdiv(a.N, BN));
     const int j = blockIdx.x / 8;
     const int tile = walk.tile(j / WALK_PER_XCD, blockIdx.x % 8, j % WALK_PER_XCD);
@@ -579,7 +619,7 @@ hipError_t launch_dma(const GemmArgs& a, hipStream_t s) {
   if (hipGetDevice(&dev) != hipSuccess) dev = 32;
 #define TP_LAUNCH(E)                                                                         \
   do {                                                                                       \
-    auto* fn = gemm_dma_kernel<BM, BN, BK, WGM, WGN, A_KC, B_KC, E, SPLIT, STAGES, SB, F16, TAIL>; \
+    auto* fn = gemm_dma_kernel<BM, BN, BK, WGM, WGN, A_KC, B_KC, E, SPLIT, STAGES, SB, F16, TAIL, GemmArgs>; \
     static std::atomic<uint32_t> attr_set{0};                                                \
     const uint32_t bit = dev < 32 ? 1u << dev : 0u;                                          \
     if (!bit || !(attr_set.load(std::memory_order_acquire) & bit)) {                         \
@@ -885,15 +925,15 @@ TileChoice choose_tiles(const GemmArgs& a, bool tail) {
 // us).  Fitted like choose_tiles (rms error 8 %): on average 2.7 % over the best
 // candidate, always 256 x 256 was 74 % over on the same sweep (widths 512-5120,
 // 64-8192 tokens).
-TileChoice choose_dw(const GemmArgs& a) {
-  static const Cand kCands[] = {{T64x64, 64, 64, 3, 0.0, 0.3745, 0.3745, 0.1047},
-                                {T128x128, 128, 128, 1, 0.598, 0.5815, 0.5815, 0.0},
-                                {T_DW256, 256, 256, 1, 1.841, 1.3978, 1.3978, 0.0}};
+constexpr Cand kDwCands[] = {{T64x64, 64, 64, 3, 0.0, 0.3745, 0.3745, 0.1047},
+                             {T128x128, 128, 128, 1, 0.598, 0.5815, 0.5815, 0.0},
+                             {T_DW256, 256, 256, 1, 1.841, 1.3978, 1.3978, 0.0}};
+TileChoice choose_dw(const GemmArgs& a, double* us = nullptr) {
   const int nkt = cdiv(a.K, 64);
   const double out = (double)a.M * a.N * 4e-6 * (a.overwrite ? 1 : 2);
   double best = 1e300;
   TileChoice pick{T_DW256, 1};
-  for (const Cand& c : kCands) {
+  for (const Cand& c : kDwCands) {
     const long tiles = (long)cdiv(a.M, c.bm) * cdiv(a.N, c.bn);
     for (int sp : kSplits) {
       if (sp > nkt || sp > 8) break;
@@ -907,10 +947,90 @@ TileChoice choose_dw(const GemmArgs& a) {
       }
     }
   }
+  if (us) *us = best;
   return pick;
 }
 
+// One launch over the products of a group with tiles of BM x BN.
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool TAIL>
+hipError_t launch_group(GemmGroup& g, hipStream_t s) {
+  constexpr int NTH = 64 * WGM * WGN;
+  constexpr size_t lds = (size_t)STAGES * (BM + BN) * 64 * 2;
+  long tiles = 0;
+  for (int p = 0; p < g.count; ++p) tiles += (long)cdiv(g.g[p].M, BM) * cdiv(g.g[p].N, BN);
+  g.walk = tiles >= 512;
+  g.first[0] = 0;
+  for (int p = 0; p < g.count; ++p) {
+    const int tm = cdiv(g.g[p].M, BM), tn = cdiv(g.g[p].N, BN);
+    // the super-tile orientation that leaves fewer idle slots
+    const int up = TileWalk(tm, tn, false).supers(), side = TileWalk(tm, tn, true).supers();
+    g.g[p].walk = side < up ? 2 : 1;
+    g.first[p + 1] = g.first[p] + (g.walk ? std::min(up, side) : tm * tn);
+  }
+  const int n = g.first[g.count], blocks = g.walk ? cdiv(n, 8) * 8 * WALK_PER_XCD : n;
+  auto* fn = gemm_dma_kernel<BM, BN, 64, WGM, WGN, false, false, EPI_ACC_F32, false, STAGES, STAGES,
+                             false, TAIL, GemmGroup>;
+  const hipError_t e = hipFuncSetAttribute((const void*)fn,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  fn<<<blocks, NTH, lds, s>>>(g);
+  return hipGetLastError();
+}
+
+// shapes of gemm_dma_bf16 for a weight-gradient product
+bool dw_covered(const GemmArgs& a) {
+  return a.M > 0 && a.N > 0 && a.K > 0 && a.epi == EPI_ACC_F32 && a.sam == 1 && a.sbn == 1 &&
+         a.sak != 1 && a.sbk != 1 && a.M % 8 == 0 && a.N % 8 == 0 && !(a.sak & 7) && !(a.sbk & 7) &&
+         !((uintptr_t)a.A & 15) && !((uintptr_t)a.B & 15) && !((uintptr_t)a.C & 15) &&
+         !(a.ldc & 3) && 65 * a.sak * 2 < (1l << 32) && 65 * a.sbk * 2 < (1l << 32);
+}
+
 }  // namespace
+
+// The weight-gradient products of a layer (count <= 4, one reduction length) in one
+// launch, where that is modelled faster than one launch each with its own tiles and
+// splits: narrow gradients fill the chip together (1024 wide, 256 tokens a slice: 36 ->
+// 28 us, 5 TB/s of gradient read and written), wide ones share their part-empty last
+// rounds (2048 wide, 2048 tokens: 238 -> 202 us; 8-way shard of 12288: 1038 -> 963 us).
+// hipErrorNotSupported: not covered, or separate launches are better.
+hipError_t gemm_dw_group(const GemmArgs* g, int count, hipStream_t s) {
+  clear_stale_error();
+  if (count < 2 || count > 4) return hipErrorNotSupported;
+  double apart = 0, out = 0;
+  for (int p = 0; p < count; ++p) {
+    if (!dw_covered(g[p]) || g[p].K != g[0].K) return hipErrorNotSupported;
+    double t;
+    choose_dw(g[p], &t);
+    apart += t + 3.13;  // launch and drain
+    out += (double)g[p].M * g[p].N * 4e-6 * (g[p].overwrite ? 1 : 2);
+  }
+  const int nkt = cdiv(g[0].K, 64);
+  double best = apart;
+  int pick = -1;
+  for (const Cand& c : kDwCands) {
+    long tiles = 0;
+    for (int p = 0; p < count; ++p) tiles += (long)cdiv(g[p].M, c.bm) * cdiv(g[p].N, c.bn);
+    const double t = 3.13 + c.main_us(tiles, nkt, false) + out * 0.1437;
+    if (t < best) best = t, pick = c.cfg;
+  }
+  if (pick < 0) return hipErrorNotSupported;
+  GemmGroup G;
+  for (int p = 0; p < count; ++p) G.g[p] = g[p];
+  G.count = count;
+  const bool tail = g[0].K % 64 != 0;
+  switch (pick) {
+    case T64x64:
+      return tail ? launch_group<64, 64, 2, 2, 3, true>(G, s)
+                  : launch_group<64, 64, 2, 2, 3, false>(G, s);
+    case T128x128:
+      return tail ? launch_group<128, 128, 4, 2, 4, true>(G, s)
+                  : launch_group<128, 128, 4, 2, 4, false>(G, s);
+    case T_DW256:
+      return tail ? launch_group<256, 256, 2, 4, 2, true>(G, s)
+                  : launch_group<256, 256, 2, 4, 2, false>(G, s);
+  }
+  return hipErrorNotSupported;
+}
 
 // Shapes the DMA path takes: 16-byte-aligned operands with a unit stride and
 // leading dimensions of whole 16-byte chunks; N, and M where A is contiguous along

@@ -352,10 +352,21 @@ tp_status wgrad_gemms(tp_stage* S, int li, int l, int n) {
       tn(F, H, n, rowp(B.dz, l, F, e), F, rowp(B.u2, l, H, e), H, (float*)G.w_fc1),
       tn(H, A, n, rowp(B.dx1, l, H, e), H, rowp(B.o, l, A, e), A, (float*)G.w_o),
       tn(3 * A, H, n, rowp(B.dqkv, l, 3 * A, e), 3 * A, rowp(B.u, l, H, e), H, (float*)G.w_qkv)};
+  double flops = 0, bytes = 0;
   for (GemmArgs& gi : g) {
     gi.overwrite = ow;
-    TRY(run_gemm(S, K_GEMM_DW, gi));
+    gi.ws = S->sc.splitk, gi.ws_elems = (long)S->sc.splitk_elems;
+    flops += 2.0 * gi.M * gi.N * gi.K, bytes += gemm_bytes(gi, e);
   }
+  if (S->dt == DT_BF16) {
+    const hipError_t st =
+        launch(S, K_GEMM_DW, flops, bytes, [&] { return gemm_dw_group(g, 4, S->stream); });
+    if (st != hipErrorNotSupported) {
+      TRY(st);
+      return TP_OK;
+    }
+  }
+  for (GemmArgs& gi : g) TRY(run_gemm(S, K_GEMM_DW, gi));
   return TP_OK;
 }
 

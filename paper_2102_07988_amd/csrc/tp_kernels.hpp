@@ -91,6 +91,9 @@ struct GemmArgs {
 };
 
 hipError_t gemm(int dtype, const GemmArgs& a, hipStream_t s);
+// Weight-gradient products (EPI_ACC_F32, one reduction length) of a bf16 stage in one
+// launch; hipErrorNotSupported (nothing enqueued) where they are to run one by one.
+hipError_t gemm_dw_group(const GemmArgs* g, int count, hipStream_t s);
 // host: the 8-column vector epilogues apply (sizes and alignment)
 bool vec8_ok(const GemmArgs& a);
 // Generic (any strides, any dtype) tiled FMA GEMM; the bf16 fast path falls back
