@@ -20,6 +20,7 @@
 // the pipeline.
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <type_traits>
 
 #include "tp_common.hpp"
@@ -255,11 +256,15 @@ __device__ inline const GemmArgs& my_product(const GemmGroup& a, int i, int* loc
 // F16: both operands are fp16 (the mixed-precision query/key/value product),
 // otherwise bf16.  TAIL: K need not be whole k-tiles; the values of the last tile
 // past K are zeroed in LDS, in both operands, between two barriers.
-template <int BM, int BN, int BK, int WGM, int WGN, bool A_KC, bool B_KC, int EPI, bool SPLIT,
-          int STAGES, int SB, bool F16, bool TAIL, typename ARGS>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_dma_kernel(ARGS args) {
+// WGK: wave groups over the reduction: group wk of WGK takes its 1/WGK of every
+// k-tile's 16-value steps, and the groups' accumulators are added in LDS before the
+// epilogue.
+template <int BM, int BN, int BK, int WGM, int WGN, int WGK, bool A_KC, bool B_KC, int EPI,
+          bool SPLIT, int STAGES, int SB, bool F16, bool TAIL, typename ARGS>
+__global__ __launch_bounds__(64 * WGM * WGN * WGK) void gemm_dma_kernel(ARGS args) {
   constexpr bool GROUP = std::is_same<ARGS, GemmGroup>::value;
-  constexpr int NTH = 64 * WGM * WGN;
+  constexpr int NTH = 64 * WGM * WGN * WGK;
+  constexpr int KSP = BK / 16 / WGK;  // 16-value steps of a wave per k-tile
   constexpr int WM = BM / WGM, WN = BN / WGN, FM = WM / 32, FN = WN / 32;
   constexpr int TILE_A = BM * BK, TILE_B = BN * BK, STAGE = TILE_A + TILE_B;  // elements
   constexpr int LPT = BK * (BM + BN) / 8 / NTH;  // DMA instructions per thread per k-tile
@@ -269,14 +274,15 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_dma_kernel(ARGS args) {
   static_assert(LPT * (STAGES - 2) <= 63, "vmcnt range");
   constexpr bool BLEAD = SB > STAGES;
   static_assert(SB == STAGES || (STAGES == 2 && SB == 3), "unsupported ring shape");
-  static_assert((BK / 16) % 2 == 0, "fragment buffers alternate per k-step across k-tiles");
+  static_assert(KSP % 2 == 0, "fragment buffers alternate per k-step across k-tiles");
+  static_assert(WGK == 1 || WGK == 2, "one or two wave groups over the reduction");
   constexpr int LPT_B = BK * BN / 8 / NTH;
   // the epilogue's wave patches take the ring stage no wave reads in the last
   // k-tile; with separate rings, or where they are larger than a stage, the LDS
   // base once every wave has left the loop
-  constexpr int PATCH = WGM * WGN * 32 * 36 * 2;  // elements
-  constexpr bool PATCH_AT_BASE = BLEAD || PATCH > STAGE;
-  static_assert(PATCH <= (BLEAD ? STAGES * TILE_A : STAGES * STAGE), "epilogue patch exceeds LDS");
+  constexpr int PATCH = WGM * WGN * WGK * 32 * 36 * 2;  // elements
+  constexpr bool PATCH_AT_BASE = BLEAD || WGK > 1 || PATCH > STAGE;
+  static_assert(PATCH <= (BLEAD && WGK == 1 ? STAGES * TILE_A : STAGES * STAGE), "epilogue patch exceeds LDS");
   extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
 
   int local = 0;  // GROUP: tile or super-tile within this workgroup's product
@@ -293,7 +299,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_dma_kernel(ARGS args) {
   const long lda = A_KC ? a.sam : a.sak;
   const long ldb = B_KC ? a.sbn : a.sbk;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;
+  const int wk = WGK > 1 ? wave / (WGM * WGN) : 0;  // wave group over the reduction
+  const int wmn = WGK > 1 ? wave % (WGM * WGN) : wave, kofs = wk * KSP * 16;
+  const int wm0 = (wmn / WGN) * WM, wn0 = (wmn % WGN) * WN;
   const int kbeg = SPLIT ? blockIdx.z * a.k_split : 0;
   const int kend = SPLIT ? min(a.K, kbeg + a.k_split) : a.K;
   const int nk = TAIL ? (kend - kbeg + BK - 1) / BK : (kend - kbeg) / BK;
@@ -472,18 +480,18 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_dma_kernel(ARGS args) {
   auto ktile = [&](int kt, auto finalc) {
     constexpr bool FINAL = decltype(finalc)::value;
 #pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) {
+    for (int ks = 0; ks < KSP; ++ks) {
       const int cur = ks & 1, nxt = cur ^ 1;
-      const bool last = ks + 1 == BK / 16;
+      const bool last = ks + 1 == KSP;
       if (!last) {
-        interleave(First{}, Yes{}, cur, nxt, kt, 16 * (ks + 1));
+        interleave(First{}, Yes{}, cur, nxt, kt, kofs + 16 * (ks + 1));
       } else if constexpr (!FINAL) {
 #pragma unroll
         for (int t = 0; t < NM / 2; ++t) mfma_at(cur, t);
         __builtin_amdgcn_sched_barrier(0);
         wait_tile(kt + 1);
         if (SPLIT) issue_next(kt + 1);
-        interleave(Half{}, Yes{}, cur, nxt, kt + 1, 0);
+        interleave(Half{}, Yes{}, cur, nxt, kt + 1, kofs);
       } else {
         interleave(First{}, No{}, cur, nxt, 0, 0);
       }
@@ -495,13 +503,49 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_dma_kernel(ARGS args) {
 
   wait_tile(0);
   issue_next(0);
-  read_frags(0, 0, 0);
+  read_frags(0, 0, kofs);
   frags_ready(0);
   if (nk > 0) {
     for (int kt = 0; kt + 1 < nk; ++kt) ktile(kt, No{});
     ktile(nk - 1, Yes{});
   }
   // every outstanding DMA has been waited for: the last iteration waited for 0
+
+  // Two wave groups: a sub-tile t of the wave tile belongs to group t % 2 (a single
+  // one to group 0); each wave leaves its sums of the partner's sub-tiles in LDS and
+  // adds the partner's to its own.
+  constexpr int T = FM * FN;
+  auto mine = [&](int t) { return WGK == 1 || (T == 1 ? wk == 0 : t % 2 == wk); };
+  if constexpr (WGK > 1) {
+    constexpr int HT = (T + 1) / 2;  // sub-tiles a wave gives away at most
+    static_assert(WGM * WGN * WGK * HT * 4096 <= 2 * ((long)STAGES * TILE_A + (long)SB * TILE_B),
+                  "exchange exceeds LDS");
+    __builtin_amdgcn_s_barrier();  // every wave has read its last fragments
+    float* ex = (float*)smem;
+    const int partner = wave ^ (WGM * WGN);
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+      if (!mine(t)) {
+#pragma unroll
+        for (int v = 0; v < 16; v += 4)
+          *(float4*)(ex + ((wave * HT + t / 2) * 4 + v / 4) * 256 + lane * 4) =
+              make_float4(acc[t / FN][t % FN][v], acc[t / FN][t % FN][v + 1],
+                          acc[t / FN][t % FN][v + 2], acc[t / FN][t % FN][v + 3]);
+      }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+      if (mine(t)) {
+#pragma unroll
+        for (int v = 0; v < 16; v += 4) {
+          const float4 x =
+              *(const float4*)(ex + ((partner * HT + t / 2) * 4 + v / 4) * 256 + lane * 4);
+          f32x16_t& c = acc[t / FN][t % FN];
+          c[v] += x.x, c[v + 1] += x.y, c[v + 2] += x.z, c[v + 3] += x.w;
+        }
+      }
+    __syncthreads();
+  }
 
   if constexpr (SPLIT || EPI == EPI_ACC_F32) {
     // fp32 outputs: each 32 x 32 sub-tile goes through a wave-private LDS patch
@@ -519,8 +563,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_dma_kernel(ARGS args) {
     };
     // fp32 +=: the destination values of the next P sub-tiles are in flight
     // while one is combined (a plain store with a.overwrite)
-    constexpr int T = FM * FN, P = T < 4 ? T : 4;
+    constexpr int P = T < 4 ? T : 4;
     const bool add = !SPLIT && !a.overwrite;
+    // a gradient that is added to slice by slice is read again soon: up to 64 MB it is
+    // left in the caches (1024 wide, 4 slices, two sequences: 1327 -> 1312 us in all)
+    const bool keep = add && (long)a.M * a.N <= (16l << 20);
     float4 pre[P][4];
     if (add && full) {
 #pragma unroll
@@ -530,6 +577,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_dma_kernel(ARGS args) {
     }
 #pragma unroll
     for (int t = 0; t < T; ++t) {
+      if (!mine(t)) continue;
       const int i = t / FN, j = t % FN;
 #pragma unroll
       for (int v = 0; v < 16; ++v)
@@ -544,10 +592,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_dma_kernel(ARGS args) {
             const float4 o = pre[t % P][q];
             x[q].x += o.x, x[q].y += o.y, x[q].z += o.z, x[q].w += o.w;
           }
-          if constexpr (SPLIT) {
+          if (SPLIT || keep) {
             *(float4*)dst_of(t, q) = x[q];
           } else {
-            // the fp32 weight gradient is not read again by this sequence's
+            // a stored fp32 weight gradient is not read again by this sequence's
             // kernels: a non-temporal store keeps it from displacing their
             // operands in the caches
             const f32x4v v = {x[q].x, x[q].y, x[q].z, x[q].w};
@@ -585,6 +633,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_dma_kernel(ARGS args) {
     for (int i = 0; i < FM; ++i)
 #pragma unroll
       for (int j = 0; j < FN; ++j) {
+        if (!mine(i * FN + j)) continue;
 #pragma unroll
         for (int v = 0; v < 16; ++v)
           patch[(8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * 36 + (lane & 31)] = acc[i][j][v];
@@ -601,10 +650,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_dma_kernel(ARGS args) {
   }
 }
 
-template <int BM, int BN, int BK, int WGM, int WGN, bool A_KC, bool B_KC, int STAGES, int SB,
-          bool SPLIT, bool F16, bool TAIL>
+template <int BM, int BN, int BK, int WGM, int WGN, int WGK, bool A_KC, bool B_KC, int STAGES,
+          int SB, bool SPLIT, bool F16, bool TAIL>
 hipError_t launch_dma(const GemmArgs& a, hipStream_t s) {
-  constexpr int NTH = 64 * WGM * WGN;
+  constexpr int NTH = 64 * WGM * WGN * WGK;
   constexpr size_t lds = ((size_t)STAGES * BM + (size_t)SB * BN) * BK * 2;
   dim3 grid(cdiv(a.N, BN), cdiv(a.M, BM), SPLIT ? a.splits : 1);
   if (!SPLIT && a.walk) {
@@ -619,7 +668,8 @@ hipError_t launch_dma(const GemmArgs& a, hipStream_t s) {
   if (hipGetDevice(&dev) != hipSuccess) dev = 32;
 #define TP_LAUNCH(E)                                                                         \
   do {                                                                                       \
-    auto* fn = gemm_dma_kernel<BM, BN, BK, WGM, WGN, A_KC, B_KC, E, SPLIT, STAGES, SB, F16, TAIL, GemmArgs>; \
+    auto* fn = gemm_dma_kernel<BM, BN, BK, WGM, WGN, WGK, A_KC, B_KC, E, SPLIT, STAGES, SB, F16, TAIL, \
+                               GemmArgs>;                                                  \
     static std::atomic<uint32_t> attr_set{0};                                                \
     const uint32_t bit = dev < 32 ? 1u << dev : 0u;                                          \
     if (!bit || !(attr_set.load(std::memory_order_acquire) & bit)) {                         \
@@ -666,8 +716,8 @@ hipError_t launch_dma(const GemmArgs& a, hipStream_t s) {
 // and 0 < cols1 < the column-tile count, the product runs as two split launches:
 // column tiles [0, cols1) with `splits`, the rest with splits2, and one reduction
 // over both.  The caller has checked that the partials fit the workspace.
-template <int BM, int BN, int BK, int WGM, int WGN, bool A_KC, bool B_KC, int STAGES, int SB,
-          bool F16, bool TAIL>
+template <int BM, int BN, int BK, int WGM, int WGN, int WGK, bool A_KC, bool B_KC, int STAGES,
+          int SB, bool F16, bool TAIL>
 hipError_t run_dma(GemmArgs a, hipStream_t s, int splits, int splits2, int cols1) {
   constexpr int CUS = 256;
   const long tiles = (long)cdiv(a.M, BM) * cdiv(a.N, BN);
@@ -679,13 +729,13 @@ hipError_t run_dma(GemmArgs a, hipStream_t s, int splits, int splits2, int cols1
     const long p1 = (long)s1 * a.M * n1;
     GemmArgs g = a;
     g.N = n1, g.k_split = ks1, g.splits = s1;
-    hipError_t e = launch_dma<BM, BN, BK, WGM, WGN, A_KC, B_KC, STAGES, SB, true, F16, TAIL>(g, s);
+    hipError_t e = launch_dma<BM, BN, BK, WGM, WGN, WGK, A_KC, B_KC, STAGES, SB, true, F16, TAIL>(g, s);
     if (e != hipSuccess) return e;
     g = a;
     g.N = n2, g.k_split = ks2, g.splits = s2;
     g.B = (const uint16_t*)a.B + (long)n1 * a.sbn;
     g.ws = a.ws + p1, g.ws_elems = a.ws_elems - p1;
-    e = launch_dma<BM, BN, BK, WGM, WGN, A_KC, B_KC, STAGES, SB, true, F16, TAIL>(g, s);
+    e = launch_dma<BM, BN, BK, WGM, WGN, WGK, A_KC, B_KC, STAGES, SB, true, F16, TAIL>(g, s);
     if (e != hipSuccess) return e;
     GemmArgs r = a;
     r.splits = s1, r.splits2 = s2, r.split_cols = n1;
@@ -694,13 +744,13 @@ hipError_t run_dma(GemmArgs a, hipStream_t s, int splits, int splits2, int cols1
   if (splits > 1) {
     a.k_split = cdiv(nkt, splits) * BK;
     a.splits = cdiv(a.K, a.k_split);
-    hipError_t e = launch_dma<BM, BN, BK, WGM, WGN, A_KC, B_KC, STAGES, SB, true, F16, TAIL>(a, s);
+    hipError_t e = launch_dma<BM, BN, BK, WGM, WGN, WGK, A_KC, B_KC, STAGES, SB, true, F16, TAIL>(a, s);
     if (e != hipSuccess) return e;
     return gemm_splitk_reduce(a, s);
   }
   // many tiles: XCD-aware super-tile order
   if (tiles >= 2 * CUS) a.walk = 1;
-  return launch_dma<BM, BN, BK, WGM, WGN, A_KC, B_KC, STAGES, SB, false, F16, TAIL>(a, s);
+  return launch_dma<BM, BN, BK, WGM, WGN, WGK, A_KC, B_KC, STAGES, SB, false, F16, TAIL>(a, s);
 }
 
 // Tile configurations.  All hold 64-value k-tiles; wpc workgroups fit a CU's LDS.
@@ -709,25 +759,37 @@ enum TileCfg { T256x256, T256x192, T256x128, T128x128, T64x128, T64x64, T32x128,
 template <bool A_KC, bool B_KC, bool F16, bool TAIL>
 hipError_t run_cfg(int cfg, const GemmArgs& a, hipStream_t s, int splits, int splits2, int cols1) {
   constexpr bool SLICE = A_KC;  // a slice's activations or gradients times a weight matrix
-  switch (cfg) {
-    case T128x128:
-      return run_dma<128, 128, 64, 4, 2, A_KC, B_KC, 4, 4, F16, TAIL>(a, s, splits, 0, 0);
-    case T64x64: return run_dma<64, 64, 64, 2, 2, A_KC, B_KC, 3, 3, F16, TAIL>(a, s, splits, 0, 0);
-  }
   if constexpr (!SLICE) {
+    if (cfg == T128x128)
+      return run_dma<128, 128, 64, 4, 2, 1, A_KC, B_KC, 4, 4, F16, TAIL>(a, s, splits, 0, 0);
+    if (cfg == T64x64)
+      return run_dma<64, 64, 64, 2, 2, 1, A_KC, B_KC, 3, 3, F16, TAIL>(a, s, splits, 0, 0);
     if (cfg == T_DW256)
-      return run_dma<256, 256, 64, 2, 4, A_KC, B_KC, 2, 2, F16, TAIL>(a, s, splits, 0, 0);
-  } else if constexpr (!TAIL) {
+      return run_dma<256, 256, 64, 2, 4, 1, A_KC, B_KC, 2, 2, F16, TAIL>(a, s, splits, 0, 0);
+  } else {
+    // Two wave groups over the reduction: a wave tile twice as large reads fewer
+    // LDS bytes per product (64x128 tiles of eight waves: 48 instead of 64 KB a
+    // k-tile), which with the DMA's writes bounds these tiles: 256 x 6144 x 2048 17.4 ->
+    // 15.8 us, 256 x 2048 x 2048 13.2 -> 11.7 us.
+    switch (cfg) {
+      case T128x128:
+        return run_dma<128, 128, 64, 2, 2, 2, A_KC, B_KC, 4, 4, F16, TAIL>(a, s, splits, 0, 0);
+      case T64x64:
+        return run_dma<64, 64, 64, 2, 2, 2, A_KC, B_KC, 3, 3, F16, TAIL>(a, s, splits, 0, 0);
+    }
+  }
+  if constexpr (SLICE && !TAIL) {
     switch (cfg) {
       case T256x256:
-        return run_dma<256, 256, 64, 2, 4, A_KC, B_KC, 2, 3, F16, false>(a, s, splits, splits2, cols1);
+        return run_dma<256, 256, 64, 2, 4, 1, A_KC, B_KC, 2, 3, F16, false>(a, s, splits, splits2, cols1);
       // 256 tiles for a 256-row product of width 49152, 64 for 12288
       case T256x192:
-        return run_dma<256, 192, 64, 4, 2, A_KC, B_KC, 2, 3, F16, false>(a, s, splits, splits2, cols1);
+        return run_dma<256, 192, 64, 4, 2, 1, A_KC, B_KC, 2, 3, F16, false>(a, s, splits, splits2, cols1);
       case T256x128:
-        return run_dma<256, 128, 64, 4, 2, A_KC, B_KC, 3, 3, F16, false>(a, s, splits, 0, 0);
-      case T64x128: return run_dma<64, 128, 64, 2, 4, A_KC, B_KC, 3, 3, F16, false>(a, s, splits, 0, 0);
-      case T32x128: return run_dma<32, 128, 64, 1, 4, A_KC, B_KC, 4, 4, F16, false>(a, s, splits, 0, 0);
+        return run_dma<256, 128, 64, 4, 2, 1, A_KC, B_KC, 3, 3, F16, false>(a, s, splits, 0, 0);
+      case T64x128:
+        return run_dma<64, 128, 64, 2, 2, 2, A_KC, B_KC, 3, 3, F16, false>(a, s, splits, 0, 0);
+      case T32x128: return run_dma<32, 128, 64, 1, 4, 1, A_KC, B_KC, 4, 4, F16, false>(a, s, splits, 0, 0);
     }
   }
   return hipErrorNotSupported;
@@ -825,33 +887,39 @@ long reference_partials(const GemmArgs& a) {
 
 // Tile shape and split count of a product whose A operand is k-contiguous (slice
 // activations or output gradients times a weight matrix): the candidate with the
-// smallest modelled time.  The model was fitted (log least squares, rms error 8 %)
+// smallest modelled time.  The model was fitted (log least squares, rms error 7 %)
 // to a sweep of every candidate (graph replays, rotating weights) on the 8 products
 // of a layer for widths 256-12288 and 8- and 4-way shards, 16-4096 rows; its pick
-// is on average 2.5 % (at worst 26 %) over the best candidate of each product,
-// where the former four shapes (128x128 and up, one workgroup a CU) were 22 % over.
+// is on average 1.1 % (at worst 32 %) over the best candidate of each product,
+// where four shapes of 128x128 and up, one workgroup a CU, were 22 % over.
 // What decides: a CU moves operands at 45-65 GB/s, more with two or three
 // workgroups on it, so narrow products want small tiles that use every CU without
-// partial sums (256 x 3072 x 1024: 14.5 -> 9 us, 256 x 8192 x 2048: 23 -> 18 us with
-// a GELU), wide ones large tiles that move few bytes per flop.
-//   t = 3.4 + max(main + GELU, weights (once from HBM, again from the caches for
-//   every further row tile) + A (for every column tile)) + (split: 2.9 + partials)
+// partial sums (256 x 3072 x 1024: 14.5 -> 9 us, 256 x 8192 x 2048 with a GELU: 23 ->
+// 17.5 us), wide ones large tiles that move few bytes per flop.
+//   t = 3.6 + |(main + GELU, stream)| + epilogue bytes + (split: 2.1 + 0.16 per
+//   split + partials)
+// with stream = the weights (once from HBM, again from the caches for every further
+// row tile) and A (for every column tile).
 TileChoice choose_tiles(const GemmArgs& a, bool tail) {
-  static const Cand kCands[] = {{T32x128, 32, 128, 2, 0.453, 0.2906, 0.4149, 0.1398},
-                                {T64x64, 64, 64, 3, 0.355, 0.3117, 0.4227, 0.1123},
-                                {T64x128, 64, 128, 2, 0.613, 0.3932, 0.4942, 0.1854},
-                                {T128x128, 128, 128, 1, 1.326, 0.5297, 0.5996, 0.0},
-                                {T256x128, 256, 128, 1, 1.624, 0.8944, 0.9446, 0.0},
-                                {T256x192, 256, 192, 1, 2.535, 1.1647, 1.2717, 0.0},
-                                {T256x256, 256, 256, 1, 3.007, 1.3868, 1.5431, 0.0}};
+  static const Cand kCands[] = {{T32x128, 32, 128, 2, 0.281, 0.2644, 0.3440, 0.1016},
+                                {T64x64, 64, 64, 3, 0.378, 0.2191, 0.3375, 0.0986},
+                                {T64x128, 64, 128, 2, 0.730, 0.3103, 0.3947, 0.1583},
+                                {T128x128, 128, 128, 1, 2.326, 0.4158, 0.4605, 0.0},
+                                {T256x128, 256, 128, 1, 1.887, 0.8262, 0.8117, 0.0},
+                                {T256x192, 256, 192, 1, 3.001, 1.1034, 1.1131, 0.0},
+                                {T256x256, 256, 256, 1, 3.427, 1.3320, 1.3828, 0.0}};
   const int nkt = cdiv(a.K, 64);
   const double wmb = (double)a.N * a.K * 2e-6, amb = (double)a.M * a.K * 2e-6;
-  const bool cold = (double)a.N * a.K >= 18e6;  // a weight matrix past the caches' share
+  // a weight matrix past the caches' share (with the line at 8e6 the 2048-wide stage
+  // took 4217 us for 4115)
+  const bool cold = (double)a.N * a.K >= 18e6;
   const long room = a.ws ? a.ws_elems : 0;
   const bool gelu = a.epi == EPI_GELU || a.epi == EPI_DGELU;
+  // MB the epilogue reads and writes
+  const double outmb = (double)a.M * a.N * 1e-6 * (a.epi == EPI_RESID ? 8 : gelu ? 4 : 2);
   auto stream_us = [&](const Cand& c, double cols) {  // for `cols` of the N columns
     const long mt = cdiv(a.M, c.bm);
-    return wmb * cols / a.N * (0.1765 + 0.0416 * (mt - 1)) + amb * 0.0557 * cdiv((long)cols, c.bn);
+    return wmb * cols / a.N * (0.1512 + 0.0253 * (mt - 1)) + amb * 0.0362 * cdiv((long)cols, c.bn);
   };
   long limit = -1;  // partial sums the plan may take; the reference plan only where needed
   auto fits = [&](double part) {
@@ -870,10 +938,12 @@ TileChoice choose_tiles(const GemmArgs& a, bool tail) {
       if (sp > nkt) break;
       const int ks = cdiv(nkt, sp), s = cdiv(nkt, ks);
       double t = c.main_us(tiles * s, ks, cold);
-      if (s == 1 && gelu) t += 2.686 * cdiv(tiles, 256) * c.bm * c.bn / 16384.0;
-      t = std::max(t, stream) + 3.361;
+      if (s == 1 && gelu) t += 1.457 * cdiv(tiles, 256) * c.bm * c.bn / 16384.0;
+      t = std::sqrt(t * t + stream * stream) + 3.563;
       const double part = s > 1 ? (double)s * a.M * a.N : 0.0;
-      if (s > 1) t += 2.887 + part * 8e-6 * 0.1638;
+      if (s > 1) t += 2.142 + 0.1614 * s + part * 8e-6 * 0.1364 + outmb * 0.1356;
+      // a LayerNorm that follows costs a launch of its own after an unsplit product
+      else t += outmb * 0.1449 + (a.norm ? 2.0 + (double)a.M * a.N * 8e-6 * 0.12 : 0.0);
       if (t < best && (s == 1 || fits(part))) {
         best = t;
         pick = {c.cfg, s, 0, 0, (long)part};
@@ -899,13 +969,15 @@ TileChoice choose_tiles(const GemmArgs& a, bool tail) {
         if (cols1 >= tn) break;
         if (cols1 * mt * e1 != r1 * 256) continue;
         const long n1 = cols1 * c.bn, n2 = a.N - n1;
-        const double t1 = std::max(c.main_us(r1 * 256, ks1, cold), stream_us(c, n1));
+        const double t1 = std::hypot(c.main_us(r1 * 256, ks1, cold), stream_us(c, n1));
         for (int sp2 : kSplits) {
           if (sp2 > nkt) break;
           const int ks2 = cdiv(nkt, sp2), e2 = cdiv(nkt, ks2);
           const double part = (double)e1 * a.M * n1 + (double)e2 * a.M * n2;
-          const double t = t1 + 2 * 3.361 + 2.887 + part * 8e-6 * 0.1638 +
-                           std::max(c.main_us(mt * (tn - cols1) * e2, ks2, cold), stream_us(c, n2));
+          const double t = t1 + 2 * 3.563 + 2.142 + 0.1614 * (e1 + e2) +
+                           part * 8e-6 * 0.1364 + outmb * 0.1356 +
+                           std::hypot(c.main_us(mt * (tn - cols1) * e2, ks2, cold),
+                                      stream_us(c, n2));
           if (t < best && t < 0.97 * single && fits(part)) {
             best = t;
             pick = {c.cfg, e1, e2, (int)cols1, (long)part};
@@ -968,7 +1040,7 @@ hipError_t launch_group(GemmGroup& g, hipStream_t s) {
     g.first[p + 1] = g.first[p] + (g.walk ? std::min(up, side) : tm * tn);
   }
   const int n = g.first[g.count], blocks = g.walk ? cdiv(n, 8) * 8 * WALK_PER_XCD : n;
-  auto* fn = gemm_dma_kernel<BM, BN, 64, WGM, WGN, false, false, EPI_ACC_F32, false, STAGES, STAGES,
+  auto* fn = gemm_dma_kernel<BM, BN, 64, WGM, WGN, 1, false, false, EPI_ACC_F32, false, STAGES, STAGES,
                              false, TAIL, GemmGroup>;
   const hipError_t e = hipFuncSetAttribute((const void*)fn,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
