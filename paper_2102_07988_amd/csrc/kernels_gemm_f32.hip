@@ -3,8 +3,8 @@
 //
 // A block of WGM x WGN waves owns a BM x BN output tile, each wave 32 FM x 32 FN
 // of it.  k-tiles of 32 values go from global memory through registers (the loads
-// of tile kt + 1 are in flight while tile kt is multiplied) into a double-buffered
-// LDS stage in the operand's own orientation:
+// of tile kt + 2 are in flight while tile kt is multiplied and tile kt + 1 is in LDS)
+// into a double-buffered LDS stage in the operand's own orientation:
 //  - k-contiguous operands as [row][32 k] (16-byte chunks permuted by the row);
 //    a lane reads 4 consecutive k of its row with one ds_read_b128;
 //  - operands contiguous along m / n as [k][R]; a lane reads its column of one k
@@ -18,8 +18,10 @@
 // products take 64 x 64 tiles for the sake of many workgroups and split the
 // reduction when they are still few, products of many tiles 128 x 128.
 // Width 1024, 256-token slices, averages over a layer's products against the
-// strided FMA kernel: forward 337 -> 24 us (+ 5 us reduction), dX 468 -> 23 us (+ 5),
-// weight gradients over 1024 tokens 253 -> 72 us.
+// strided FMA kernel: forward 337 -> 23 us (+ 5 us reduction), dX 468 -> 22 us (+ 5),
+// weight gradients over 1024 tokens 253 -> 72 us.  About 60 % of the fp32 matrix rate;
+// reading the fragments a step ahead, or one workgroup a CU without splits, was 2-4 %
+// slower over the layer.
 #include "tp_common.hpp"
 #include "tp_epilogue.hpp"
 #include "tp_kernels.hpp"
@@ -55,29 +57,29 @@ struct Tile32 {
     if constexpr (KC) return make_int2(s >> 3, (s & 7) * 4);
     else return make_int2((s % (R / 4)) * 4, s / (R / 4));
   }
+  unsigned ok;  // bit i: chunk i lies inside the operand
+  // A chunk is inside or outside as a whole (the contiguous extent is a multiple of
+  // 4).  Outside ones load the nearest valid chunk and are cleared when stored: no
+  // branch around a load, which would wait for it where the paths join.
   __device__ void load(const float* X, long ld, int r0, int rmax, int k0, int kmax) {
+    ok = 0;
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
       const int2 p = at(i);
       const int r = r0 + p.x, k = k0 + p.y;
-      // values along the contiguous dimension that exist
-      const int have = KC ? (r < rmax ? kmax - k : 0) : (k < kmax ? rmax - r : 0);
-      const float* src = KC ? X + (long)r * ld + k : X + (long)k * ld + r;
-      v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (have >= 4) {
-        v[i] = *(const float4*)src;
-      } else if (have > 0) {
-        v[i].x = src[0];
-        if (have > 1) v[i].y = src[1];
-        if (have > 2) v[i].z = src[2];
-      }
+      ok |= (r < rmax && k < kmax ? 1u : 0u) << i;
+      const int rc = min(r, KC ? rmax - 1 : rmax - 4), kc = min(k, KC ? kmax - 4 : kmax - 1);
+      v[i] = *(const float4*)(KC ? X + (long)rc * ld + kc : X + (long)kc * ld + rc);
     }
   }
   __device__ void store(float* lds) const {
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
       const int2 p = at(i);
-      *(float4*)(lds + (KC ? kc_off(p.x, p.y) : mc_off<R>(p.y, p.x))) = v[i];
+      const bool in = (ok >> i) & 1;
+      const float4 x = make_float4(in ? v[i].x : 0.f, in ? v[i].y : 0.f, in ? v[i].z : 0.f,
+                                   in ? v[i].w : 0.f);
+      *(float4*)(lds + (KC ? kc_off(p.x, p.y) : mc_off<R>(p.y, p.x))) = x;
     }
   }
   // values k = 8 i + 4 G + e (e < 4) of row / column r
@@ -130,10 +132,15 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_f32_kernel(GemmArgs a) {
     load(0);
     ta.store(As[0]);
     tb.store(Bs[0]);
+    if (nk > 1) load(1);
   }
   for (int kt = 0; kt < nk; ++kt) {
     __syncthreads();  // tile kt is in LDS; every wave has left tile kt - 1
-    if (kt + 1 < nk) load(kt + 1);
+    if (kt + 1 < nk) {
+      ta.store(As[(kt + 1) & 1]);
+      tb.store(Bs[(kt + 1) & 1]);
+    }
+    if (kt + 2 < nk) load(kt + 2);
     const float* at = As[kt & 1];
     const float* bt = Bs[kt & 1];
 #pragma unroll
@@ -150,10 +157,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_f32_kernel(GemmArgs a) {
 #pragma unroll
           for (int y = 0; y < FN; ++y)
             acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[x][e], fb[y][e], acc[x][y], 0, 0, 0);
-    }
-    if (kt + 1 < nk) {
-      ta.store(As[(kt + 1) & 1]);
-      tb.store(Bs[(kt + 1) & 1]);
     }
   }
   // acc[x][y][v]: row 8 (v / 4) + 4 G + v % 4, column c of the 32 x 32 tile
@@ -250,8 +253,9 @@ hipError_t run_f32(GemmArgs a, hipStream_t s) {
 
 }  // namespace
 
-// fp32 operands with a unit stride, 16-byte-aligned bases and leading dimensions
-// of whole 16-byte chunks; anything else is left to the strided kernel.
+// fp32 operands with a unit stride, 16-byte-aligned bases, leading dimensions and
+// contiguous extents of whole 16-byte chunks; anything else is left to the strided
+// kernel.
 hipError_t gemm_f32(const GemmArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
   const bool a_kc = a.sak == 1, b_kc = a.sbk == 1;
@@ -259,6 +263,8 @@ hipError_t gemm_f32(const GemmArgs& a, hipStream_t s) {
   const long lda = a_kc ? a.sam : a.sak, ldb = b_kc ? a.sbn : a.sbk;
   if (((uintptr_t)a.A & 15) || ((uintptr_t)a.B & 15) || (lda & 3) || (ldb & 3))
     return hipErrorNotSupported;
+  // whole 4-value chunks along the contiguous dimension of each operand
+  if (a.K <= 0 || (a_kc ? a.K : a.M) % 4 || (b_kc ? a.K : a.N) % 4) return hipErrorNotSupported;
   if (a_kc && b_kc) return run_f32<true, true>(a, s);
   if (a_kc) return run_f32<true, false>(a, s);
   if (!b_kc) return run_f32<false, false>(a, s);
