@@ -1283,9 +1283,12 @@ template <int D, bool F16>
 hipError_t bwd_d(const AttnArgs& a, hipStream_t s) {
   const int n = a.r - a.l;
   if (a.need) return dq_d<D, F16>(a, s);  // only the dQ kernel takes split scratch
-  attn_bwd_rowdot<D><<<dim3(cdiv((long)n * a.heads, 4), 1, a.bs), 256, 0, s>>>(a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  hipError_t e = hipSuccess;
+  if (!a.have_D) {
+    attn_bwd_rowdot<D><<<dim3(cdiv((long)n * a.heads, 4), 1, a.bs), 256, 0, s>>>(a);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   if ((long)cdiv(a.r, 128) * a.heads * a.bs < 128) {
     // few key blocks (few heads, short prefix): four-wave blocks over two-tile
     // rings, so more blocks share the CUs

@@ -303,6 +303,28 @@ __global__ __launch_bounds__(256) void splitk_reduce8_kernel(GemmArgs a) {
   }
 }
 
+// The split reduction of dO with D = rowsum(dO * O) (RowDot): the d / 8 threads of a
+// head's row are neighbouring lanes of one wave.  Takes dO as stored (bf16).  Saves the
+// launch that reads dO and O once more: 256 x 2048, 4.5 + 4.1 us -> 4.9 us.
+__global__ __launch_bounds__(256) void splitk_reduce_dot_kernel(GemmArgs a, RowDot rd) {
+  const long tot8 = (long)a.M * a.N / 8;
+  const int n8 = a.N / 8, lanes = rd.d / 8;  // 8 or 16
+  for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < tot8; e += (long)gridDim.x * 256) {
+    const int m = (int)(e / n8), n = (int)(e % n8) * 8;
+    float s[8], o[8];
+    ld8((const bf16*)rd.o + (long)m * a.N + n, o);
+    sum_planes8(a, m, n, s);
+    st8((bf16*)a.C + (long)m * a.ldc + n, s);
+    float t = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) t += to_f32(from_f32<bf16>(s[i])) * o[i];
+    // whole heads are active or not: N and the element count are multiples of d
+    for (int x = lanes >> 1; x > 0; x >>= 1) t += __shfl_xor(t, x, 64);
+    if (e % lanes == 0)
+      rd.D[((long)(m % rd.bs) * rd.heads + n / rd.d) * rd.Lmax + rd.l + m / rd.bs] = t;
+  }
+}
+
 // Split reduction of a product that a LayerNorm follows (RowNorm): one block per row
 // of N <= 16384 columns, thread t owns the 8-column chunks t + blockDim.x * c, c <
 // CPT.  The row stays in registers from the partial sums to the LayerNorm output;
@@ -474,6 +496,11 @@ hipError_t launch_reduce(const GemmArgs& a, hipStream_t s) {
   }
   if (vec8_ok(a)) {
     const int blocks = (int)std::min<long>(cdiv(tot / 8, 256), 4096);
+    if (a.dot && a.epi == EPI_STORE && !a.bias && a.N == a.dot->heads * a.dot->d) {
+      splitk_reduce_dot_kernel<<<blocks, 256, 0, s>>>(a, *a.dot);
+      *a.dot_done = true;
+      return hipGetLastError();
+    }
     switch (a.epi) {
 #define TP_CASE(E) \
   case E: splitk_reduce8_kernel<E><<<blocks, 256, 0, s>>>(a); break;

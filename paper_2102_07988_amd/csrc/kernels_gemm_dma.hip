@@ -942,8 +942,10 @@ TileChoice choose_tiles(const GemmArgs& a, bool tail) {
       t = std::sqrt(t * t + stream * stream) + 3.563;
       const double part = s > 1 ? (double)s * a.M * a.N : 0.0;
       if (s > 1) t += 2.142 + 0.1614 * s + part * 8e-6 * 0.1364 + outmb * 0.1356;
-      // a LayerNorm that follows costs a launch of its own after an unsplit product
-      else t += outmb * 0.1449 + (a.norm ? 2.0 + (double)a.M * a.N * 8e-6 * 0.12 : 0.0);
+      // a LayerNorm (or D) that follows costs a launch of its own after an unsplit
+      // product
+      else t += outmb * 0.1449 + (a.norm ? 2.0 + (double)a.M * a.N * 8e-6 * 0.12 : 0.0) +
+                (a.dot ? 2.5 + (double)a.M * a.N * 4e-6 * 0.12 : 0.0);
       if (t < best && (s == 1 || fits(part))) {
         best = t;
         pick = {c.cfg, s, 0, 0, (long)part};

@@ -536,6 +536,12 @@ tp_status backward_impl(tp_stage* S, int l, int r, const void* dy, void* dx) {
     // output projection backward: dO = dx1 W_o
     g = nn(n, A, H, rowp(B.dx1, lr, H, e), H, P.w_o);
     g.C = S->sc.dout, g.ldc = A;
+    // (the matrix-core attention's D with it, where the product is split)
+    RowDot rd;
+    bool have_D = false;
+    rd.o = rowp(B.o, lr, A, e), rd.D = S->sc.D;
+    rd.d = S->d, rd.heads = S->heads, rd.Lmax = S->L, rd.l = l, rd.bs = S->bsz;
+    if (mx) g.dot = &rd, g.dot_done = &have_D;
     TRY(run_gemm(S, K_GEMM_DX, g));
     // attention backward: dq rows, dK/dV into the fp32 buffer for keys [0, r)
     AttnArgs a;
@@ -547,7 +553,7 @@ tp_status backward_impl(tp_stage* S, int l, int r, const void* dy, void* dx) {
     a.q = rowp(B.q, lr, A, e), a.kc = B.kc, a.o = rowp(B.o, lr, A, e), a.lse = B.lse;
     a.vc = mx ? B.vb : B.vc;  // the backward's values are bf16
     a.f16 = mx;
-    a.dout = S->sc.dout, a.D = S->sc.D;
+    a.dout = S->sc.dout, a.D = S->sc.D, a.have_D = have_D;
     a.dq = rowp(B.dqkv, lr, 3 * A, e), a.ld_dq = (long)S->bsz * 3 * A, a.dq_seq = 3 * A;
     a.dk = B.dk, a.dv = B.dv;
     // the sequence's first backward slice finds no sums in the buffers; the slice's

@@ -40,6 +40,16 @@ struct RowNorm {
   void *resid_copy = nullptr, *dx = nullptr;
 };
 
+// D = rowsum(dO * O) of the attention backward, for the product that forms dO (N
+// columns, heads of d = 64 or 128): a launcher that reduces split partial sums has the
+// rows in registers and saves the launch that would read them back.  Row m is token
+// l + m / bs of sequence m % bs; o: rows of N bf16; D: fp32 [bs][heads][Lmax].
+struct RowDot {
+  const void* o = nullptr;
+  float* D = nullptr;
+  int d = 0, heads = 0, Lmax = 0, l = 0, bs = 1;
+};
+
 struct GemmArgs {
   int M = 0, N = 0, K = 0;
   const void* A = nullptr;  // A(m,k) = A[m*sam + k*sak]
@@ -72,6 +82,9 @@ struct GemmArgs {
   // sums; *norm_done tells whether it has (else the caller launches it)
   const RowNorm* norm = nullptr;
   bool* norm_done = nullptr;
+  // the same for the attention backward's D (EPI_STORE)
+  const RowDot* dot = nullptr;
+  bool* dot_done = nullptr;
   // fp32 scratch for split-K partial sums (may be null: no split)
   float* ws = nullptr;
   long ws_elems = 0;
@@ -121,6 +134,7 @@ struct AttnArgs {
   // backward
   const void* dout = nullptr;  // the slice's rows
   float* D = nullptr;          // fp32 [bs][heads][Lmax] scratch: rowsum(dO * O)
+  bool have_D = false;         // D already holds the slice's rows
   void* dq = nullptr;          // the slice's rows, ld_dq elements apart
   long ld_dq = 0, dq_seq = 0;
   float* dk = nullptr;  // fp32 accumulation buffers (absolute rows)
