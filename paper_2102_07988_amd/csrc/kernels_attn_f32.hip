@@ -82,20 +82,72 @@ struct Shape {
   static constexpr size_t part = (size_t)NW * 32 * W * 4;  // bytes of the waves' partials
 };
 
+__device__ inline bool nonfinite(float x) {
+  return (__float_as_uint(x) & 0x7f800000u) == 0x7f800000u;
+}
+
+// The part of acc_cols that X's infinities and NaNs contribute: w * X of every pair
+// that `sees` (tile row, lane's or accumulator row's column) admits.  Rarely run.
+template <int D, bool LEFT, typename T, typename S>
+__device__ inline void acc_nonfinite(const T* X, long ld, int rows, const f32x16_t& w, int G,
+                                     int c, f32x16_t (&acc)[Shape<D>::JB], S sees) {
+  constexpr int JB = Shape<D>::JB;
+#pragma unroll 1
+  for (int rr = 0; rr < rows; ++rr) {
+    const int vr = 4 * (rr >> 3) + (rr & 3), half = ((rr >> 2) & 1) << 5;  // rr = acc_row(vr, half)
+    float wr = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) wr = v == vr ? w[v] : wr;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int other = LEFT ? c : acc_row(v, G);  // the pair's query (LEFT) or key
+      const float p = __shfl(wr, half + other, 64);
+#pragma unroll
+      for (int j = 0; j < JB; ++j) {
+        const int col = 32 * j + (LEFT ? acc_row(v, G) : c);
+        const float x = tp::ld(X + (long)rr * ld + (col & (D - 1)));
+        if (nonfinite(x) && sees(rr, other)) acc[j][v] += p * x;
+      }
+      __builtin_amdgcn_sched_barrier(0);  // few registers rather than many loads in flight
+    }
+  }
+}
+
 // acc[j][v] += sum over the 32 rows of X (from row 0 of the tile, rows past
 // rows - 1 repeat it; their weights are 0): X[row][32 j + c] * w[v].  As the left
 // operand: acc^T (columns of X by lanes' columns).  `left` picks the side of X.
-template <int D, bool LEFT, typename T>
+// part: some weights of the tile are 0 because the mask or the tile's end took the
+// pair out (sees(row, other) is false).  Such a pair adds nothing also where X is
+// infinite or NaN, so a tile with such values multiplies zeros in their place and adds
+// what the admitted pairs make of them.
+template <int D, bool LEFT, typename T, typename S>
 __device__ inline void acc_cols(const T* X, long ld, int rows, const f32x16_t& w, int G, int c,
-                                f32x16_t (&acc)[Shape<D>::JB]) {
+                                f32x16_t (&acc)[Shape<D>::JB], bool part, S sees) {
   constexpr int JB = Shape<D>::JB;
   const int cc = D < 32 ? c & (D - 1) : c;  // width 16: columns 16..31 are discarded
   float x[JB][16];
+  auto load = [&](bool finite) {
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const T* r = X + (long)min(acc_row(v, G), rows - 1) * ld + cc;
+    for (int v = 0; v < 16; ++v) {
+      const T* r = X + (long)min(acc_row(v, G), rows - 1) * ld + cc;
 #pragma unroll
-    for (int j = 0; j < JB; ++j) x[j][v] = tp::ld(r + 32 * j);
+      for (int j = 0; j < JB; ++j) {
+        const float y = tp::ld(r + 32 * j);
+        x[j][v] = finite && nonfinite(y) ? 0.f : y;
+      }
+    }
+  };
+  load(false);
+  if (part) {
+    bool bad = false;
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+#pragma unroll
+      for (int j = 0; j < JB; ++j) bad |= nonfinite(x[j][v]);
+    if (__any(bad)) {
+      acc_nonfinite<D, LEFT>(X, ld, rows, w, G, c, acc, sees);
+      load(true);
+    }
   }
 #pragma unroll
   for (int v = 0; v < 16; ++v)
@@ -181,7 +233,8 @@ __global__ __launch_bounds__(64 * Shape<D>::NW) void attn_fwd_f32_kernel(AttnArg
     for (int j = 0; j < JB; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) o[j][v] *= alpha;
-    acc_cols<D, true>(V + (long)k0 * H, H, rows, p, G, c, o);
+    acc_cols<D, true>(V + (long)k0 * H, H, rows, p, G, c, o, k0 + 31 > q_lo,
+                      [&](int row, int q) { return k0 + row <= q_lo + q; });
   }
   if (G == 0) ms[w][c] = m, ls[w][c] = lsum;
   put_rows<D>(sm, w, G, c, o);
@@ -236,9 +289,11 @@ __global__ __launch_bounds__(64 * Shape<D>::NW) void attn_dq_f32_kernel(AttnArgs
     p = dot_tile<D>(kf, qf);
     dp = dot_tile<D>(vf, of);
 #pragma unroll
-    for (int v = 0; v < 16; ++v)
-      p[v] = k0 + acc_row(v, G) <= t
-                 ? __builtin_amdgcn_exp2f(__builtin_fmaf(p[v], sl2, -lse2)) : 0.f;
+    for (int v = 0; v < 16; ++v) {
+      const bool ok = k0 + acc_row(v, G) <= t;
+      p[v] = ok ? __builtin_amdgcn_exp2f(__builtin_fmaf(p[v], sl2, -lse2)) : 0.f;
+      dp[v] = ok ? dp[v] : 0.f;  // a later token's value may be infinite or NaN
+    }
   };
   float Dt = 0.f;
   if constexpr (sizeof(T) == 4) {
@@ -271,7 +326,8 @@ __global__ __launch_bounds__(64 * Shape<D>::NW) void attn_dq_f32_kernel(AttnArgs
     scores(k0, rows, p, dp);
 #pragma unroll
     for (int v = 0; v < 16; ++v) p[v] *= dp[v] - Dt;
-    acc_cols<D, true>(K + (long)k0 * H, H, rows, p, G, c, dq);
+    acc_cols<D, true>(K + (long)k0 * H, H, rows, p, G, c, dq, k0 + 31 > q_lo,
+                      [&](int row, int q) { return k0 + row <= q_lo + q; });
   }
   put_rows<D>(sm, w, G, c, dq);
   __syncthreads();
@@ -335,10 +391,12 @@ __global__ __launch_bounds__(64 * Shape<D>::NW) void attn_dkdv_f32_kernel(AttnAr
       const int i = acc_row(v, G);
       const bool ok = i < rows && key <= a.l + i0 + i;
       p[v] = ok ? __builtin_amdgcn_exp2f(__builtin_fmaf(p[v], sl2, -lq[v])) : 0.f;
-      ds[v] = p[v] * (ds[v] - dr[v]);
+      ds[v] = ok ? p[v] * (ds[v] - dr[v]) : 0.f;
     }
-    acc_cols<D, false>(dO + (long)i0 * H, H, rows, p, G, c, dv);
-    acc_cols<D, false>(Q + (long)i0 * H, H, rows, ds, G, c, dk);
+    const bool part = k_lo + 31 > a.l + i0 || rows < 32;
+    auto sees = [&](int row, int k) { return k_lo + k <= a.l + i0 + row; };
+    acc_cols<D, false>(dO + (long)i0 * H, H, rows, p, G, c, dv, part, sees);
+    acc_cols<D, false>(Q + (long)i0 * H, H, rows, ds, G, c, dk, part, sees);
   }
   // dk[j][v], dv[j][v]: key k_lo + acc_row(v), column 32 j + c; each element of the
   // fp32 buffers (or, once final, of the dqkv rows) belongs to one thread
