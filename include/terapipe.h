@@ -196,9 +196,13 @@ tp_status tp_slice_forward(tp_stage *stage, int l, int r, const void *x, void *y
  * workspace.  Nothing is allocated: no device or host memory, no events (kernel
  * timing is not recorded for this call).  The kernels and their split plans are
  * those tp_slice_forward would use, so the results are the same.  The plan is
- * made on the host first: a slice whose largest partial-sum buffer exceeds
- * 32 MiB is rejected with TP_ERR_WORKSPACE and the stage left unchanged (this
- * check precedes the one for a started sequence).  The
+ * made on the host first: a slice is rejected with TP_ERR_WORKSPACE and the
+ * stage left unchanged when the largest partial-sum buffer of one of its
+ * kernels exceeds 32 MiB (this check precedes the one for a started sequence).
+ * For the GEMMs that is the larger of the split plan that runs and of a fixed
+ * reference plan of the library, so which slices are admitted depends on their
+ * shapes alone and not on the tiles a version of the library chooses: a slice
+ * is refused also where only the reference plan exceeds the array.  The
  * array keeps whatever the last call left in it (no contents carry meaning
  * across calls); calls that overlap on one device race on it, as do
  * overlapping calls of different stages on one device.  Other arguments,

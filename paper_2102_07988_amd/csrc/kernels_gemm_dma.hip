@@ -814,17 +814,15 @@ struct Cand {
 struct TileChoice {
   int cfg, splits;
   int splits2 = 0, cols1 = 0;  // two column groups (see run_dma), 0: one launch
-  long partials = 0;           // fp32 partial sums it takes
+  long partials = 0;           // fp32 partial sums it takes at most
 };
 
-// fp32 partial sums that the static scratch of tp_slice_forward_static holds
-constexpr long STATIC_ELEMS = (32l << 20) / 4;
-
-// The partial sums by which tp_slice_forward_static admits a slice: those of a
-// reference plan over four tile shapes (128x128 .. 256x256; for row counts off the
-// 8-row grid or a K off the 64-value grid, three workgroups a CU), kept as it was
-// when the admission was defined, so that a plan that takes less scratch changes
-// no answer of that call.
+// The partial sums of the reference plan, which defines together with the plan that
+// runs which slices tp_slice_forward_static admits: four tile shapes (128x128 ..
+// 256x256; for row counts off the 8-row grid or a K off the 64-value grid, three
+// workgroups a CU) with fixed costs.  No launch follows it; it keeps that call's
+// answers the same when the tiles of choose_tiles change.  choose_tiles in turn takes
+// no more than the larger of the array and this, so an admitted slice's own plan fits.
 long reference_partials(const GemmArgs& a) {
   if (a.M % 8 || a.K % 64) {
     const int bm = a.M <= 64 ? 64 : a.M <= 128 ? 128 : a.M <= 256 ? 256 : 128;
@@ -924,8 +922,8 @@ TileChoice choose_tiles(const GemmArgs& a, bool tail) {
   long limit = -1;  // partial sums the plan may take; the reference plan only where needed
   auto fits = [&](double part) {
     if (part > room) return false;
-    if (part <= STATIC_ELEMS) return true;
-    if (limit < 0) limit = std::max(STATIC_ELEMS, reference_partials(a));
+    if (part <= STATIC_SCRATCH_ELEMS) return true;
+    if (limit < 0) limit = std::max(STATIC_SCRATCH_ELEMS, reference_partials(a));
     return part <= limit;
   };
   double best = 1e300;
@@ -1137,11 +1135,14 @@ hipError_t gemm_dma_bf16(const GemmArgs& a, hipStream_t s) {
   // fp16 operands: the query/key/value product (activations times the fp16 weight
   // copy) of stages whose widths are whole k-tiles
   if (a.in_f16 && (!b_kc || a.epi != EPI_QKV || tail)) return hipErrorNotSupported;
+  const TileChoice c = choose_tiles(a, tail);
   if (a.need) {
-    *a.need = reference_partials(a);
+    // neither plan takes more than 16 splits: below that the reference plan's search
+    // cannot change the admission
+    const bool small = 16l * a.M * a.N <= STATIC_SCRATCH_ELEMS;
+    *a.need = small ? c.partials : std::max(c.partials, reference_partials(a));
     return hipSuccess;
   }
-  const TileChoice c = choose_tiles(a, tail);
   if (a.in_f16)
     return run_cfg<true, true, true, false>(c.cfg, a, s, c.splits, c.splits2, c.cols1);
   if (tail)

@@ -230,11 +230,11 @@ hipError_t run_f32(GemmArgs a, hipStream_t s) {
   }
   // Split count: a round is two workgroups on each CU, whose waves share the
   // matrix cores (about 0.9 us per k-tile); a split adds the reduction launch and
-  // the partials' round trip.  The partials stay within 32 MiB, the capacity of
-  // the static scratch, so a split never makes the static forward refuse a slice.
+  // the partials' round trip.  The partials stay within the capacity of the static
+  // scratch, so a split never makes the static forward refuse a slice.
   const long tiles = (long)cdiv(a.M, 64) * cdiv(a.N, 64);
   const int nkt = cdiv(a.K, BK);
-  const long cap = std::min<long>(a.ws ? a.ws_elems : 0, 8l << 20);
+  const long cap = std::min<long>(a.ws ? a.ws_elems : 0, STATIC_SCRATCH_ELEMS);
   double best = 1e30;
   for (int sp = 1; sp <= 16 && sp * 4 <= std::max(nkt, 4); ++sp) {
     if (sp > 1 && (long)sp * a.M * a.N > cap) break;

@@ -98,7 +98,7 @@ struct tp_stage {
   bool w16_valid = false;
   bool profiling = false;
   // planning pass (tp_slice_forward_static): no launch, only the largest
-  // partial-sum scratch (fp32 elements) the slice's kernels would take
+  // partial-sum scratch (fp32 elements) by which the slice's kernels are admitted
   bool dry = false;
   long dry_need = 0;
   // timing
@@ -685,8 +685,9 @@ tp_status tp_slice_forward_static(tp_stage* S, int l, int r, const void* x, void
   if (l != S->cached_len || S->bwd_frontier != S->cached_len) return TP_ERR_ORDER;
   // plan the slice exactly as tp_slice_forward would run it (same split
   // choices), nothing enqueued: the largest partial-sum scratch any of its
-  // kernels takes must fit the static array.  The plan reads only the shapes,
-  // so it is checked before whether a sequence has been started.
+  // kernels takes must fit the static array, and so must that of the GEMMs'
+  // reference plan (GemmArgs::need).  The plans read only the shapes, so this is
+  // checked before whether a sequence has been started.
   S->dry = true;
   S->dry_need = 0;
   tp_status s = forward_impl(S, l, r, x, y);

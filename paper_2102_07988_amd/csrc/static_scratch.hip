@@ -11,9 +11,10 @@
 
 #include <mutex>
 
+#include "tp_kernels.hpp"
+
 namespace tp {
 
-constexpr size_t STATIC_SCRATCH_BYTES = (size_t)32 << 20;  // 32 MiB
 constexpr int MAX_DEVICES = 64;
 
 static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];

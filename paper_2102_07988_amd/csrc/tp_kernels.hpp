@@ -11,6 +11,11 @@ namespace tp {
 
 enum Dtype { DT_BF16 = 0, DT_FP32 = 1 };
 
+// The per-device array (static_scratch.hip) that holds the partial sums of
+// tp_slice_forward_static, and its fp32 elements.
+constexpr size_t STATIC_SCRATCH_BYTES = (size_t)32 << 20;
+constexpr long STATIC_SCRATCH_ELEMS = (long)(STATIC_SCRATCH_BYTES / 4);
+
 // GEMM epilogues (what happens to acc = sum_k A(m,k) B(k,n), fp32):
 enum EpiKind {
   EPI_STORE = 0,  // C[m][n] = acc (+ bias[n])
@@ -97,9 +102,12 @@ struct GemmArgs {
   int split_cols = 0, splits2 = 0;
   // set by the launcher: output-tile order (0 grid order, 1 XCD super-tiles)
   int walk = 0;
-  // Host-side planning: when set, the launcher launches nothing and stores
-  // the fp32 scratch elements (split-K partials) its plan for this product
-  // takes, 0 without a split.  The caller zeroes *need first.
+  // Host-side planning (tp_slice_forward_static): when set, the launcher launches
+  // nothing and stores the fp32 scratch elements by which the product is admitted to
+  // the static array: never fewer than the split-K partials of the plan that a launch
+  // with the same arguments follows, and where the product could outgrow the array
+  // those of the reference plan if they are more (kernels_gemm_dma.hip).  The caller
+  // zeroes *need first.
   long* need = nullptr;
 };
 
