@@ -1196,13 +1196,15 @@ hipError_t dq_d(const AttnArgs& a, hipStream_t s) {
 // tile loads.  Launches of up to 128 blocks split to about two blocks per CU (what
 // their LDS allows), at least 256 keys a split: 16 heads, 512 queries after up to 7680
 // keys, 69 -> 31 us (+ 7 us combine); 256 queries after up to 1792, 25 -> 10 us (+ 5).
+// Fewer keys a split don't pay (64 heads, 100 queries, 257 to 500 keys, 2 splits of
+// 129-250: 2 us slower than one).
 // 192 blocks (96 heads, 256 queries) are faster unsplit: 30 us against 34 + 9.
 void plan_stream_split(AttnArgs& a) {
   a.nsplit = 1;
   const int n = a.r - a.l;
   const long wgs = (long)cdiv(n, 128) * a.heads * a.bs;
   if (!a.ws || wgs > 128) return;
-  int ns = (int)std::min<long>({MAX_SPLIT, cdiv(512, wgs), cdiv(a.r, 256)});
+  int ns = (int)std::min<long>({MAX_SPLIT, cdiv(512, wgs), a.r / 256});
   while (ns > 1 && (long)ns * n * a.bs * a.H > a.ws_elems) --ns;
   if (ns < 2) return;
   a.kv_chunk = cdiv(cdiv(a.r, ns), 64) * 64;

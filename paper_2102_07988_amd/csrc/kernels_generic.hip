@@ -409,10 +409,10 @@ hipError_t col_reduce(int dtype, int x_f32, ColJobs J, hipStream_t s) {
     slots += j.cols * (j.x ? 2 : 1);
   }
   J.slots = slots;
-  // about 1024 blocks (4 per CU), at most 16 chunks of at least 256 rows (of a
-  // 256-row slice, two chunks and their second launch took 10 us for 8); the
-  // partials must fit
-  J.chunks = (int)std::min<long>({16, cdiv(J.rows, 256), std::max(1, cdiv(1024, blocks))});
+  // about 1024 blocks (4 per CU), at most 16 chunks of at least 256 rows (a 256-row
+  // slice in two chunks, with their second launch, took 10 us for 8; 300 rows in two of
+  // 150, 1024 wide, 2.2 us more than in one); the partials must fit
+  J.chunks = (int)std::min<long>({16, std::max(1, J.rows / 256), std::max(1, cdiv(1024, blocks))});
   while (J.chunks > 1 && (!J.part || (long)J.chunks * slots > J.part_elems)) --J.chunks;
   J.rows_per = cdiv(J.rows, J.chunks);
   J.chunks = cdiv(J.rows, J.rows_per);

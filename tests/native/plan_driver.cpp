@@ -6,6 +6,8 @@
 //
 // Prints one line per product whose launch takes more scratch than the admission said
 // or writes past the array that the admission grants, and "products N, split S".
+// Also the least work of a part: column sums over rows in chunks of at least 256 rows,
+// the streaming dQ kernel in key splits of at least 256 keys.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -17,6 +19,8 @@
 namespace {
 long recorded = 0;  // most fp32 partial sums among the launches since it was cleared
 int launches = 0;
+enum { GEMM, COLSUM, ATTN } kind = GEMM;  // what the launches' first argument is
+int least = 0;                            // rows of a chunk, keys of a split (0: unsplit)
 dim3 grid_, block_;
 size_t lds_;
 hipStream_t stream_;
@@ -26,6 +30,16 @@ hipStream_t stream_;
 // split_cols and splits2 as set by the launcher).
 extern "C" hipError_t hipLaunchKernel(const void*, dim3 grid, dim3, void** args, size_t,
                                       hipStream_t) {
+  if (kind == COLSUM) {
+    const tp::ColJobs& j = *(const tp::ColJobs*)args[0];
+    least = j.chunks > 1 ? j.rows_per : 0;
+    return hipSuccess;
+  }
+  if (kind == ATTN) {
+    const tp::AttnArgs& a = *(const tp::AttnArgs*)args[0];
+    if (a.nsplit > 1) least = a.kv_chunk;
+    return hipSuccess;
+  }
   const tp::GemmArgs& a = *(const tp::GemmArgs*)args[0];
   long n = 0;
   if (a.split_cols)
@@ -94,6 +108,45 @@ int main() {
             }
           }
   std::printf("products %d, split %d\n", products, split);
+  int chunked = 0, kv_split = 0;
+  kind = COLSUM;
+  for (int H : {64, 256, 512, 1024, 2048, 4096, 12288})
+    for (int rows = 1; rows <= 4200; rows += rows < 1100 ? 1 : 97) {
+      ColJobs J;
+      const int cols[6] = {H, 4 * H, H, H, 3 * H, H};
+      for (int i = 0; i < 6; ++i) {
+        J.job[i].a = base, J.job[i].cols = J.job[i].lda = cols[i], J.job[i].sum = (float*)base;
+        if (i == 2 || i == 5) J.job[i].x = base, J.job[i].xsum = (float*)base;
+      }
+      J.count = 6, J.rows = rows, J.part = (float*)base;
+      J.part_elems = 8l * std::min(rows, 256) * 4 * H;
+      least = 0;
+      if (col_reduce(DT_BF16, 1, J, nullptr) != hipSuccess) ++bad;
+      chunked += least > 0;
+      if (least > 0 && least < 256 && ++bad <= 20)
+        std::printf("column sums: H %d, %d rows in chunks of %d\n", H, rows, least);
+    }
+  kind = ATTN;
+  for (int heads : {8, 16, 32, 64, 128})
+    for (int n : {1, 16, 100, 128, 256, 512})
+      for (int r = n; r <= 4096; r += r < 1100 ? 1 : 37) {
+        // shorter prefixes take the recomputing dQ kernel
+        if ((r + 127) / 128 * heads < 128) continue;
+        AttnArgs a;
+        a.l = r - n, a.r = r, a.d = 128, a.heads = heads, a.H = a.ld = heads * 128;
+        a.Lmax = 4096, a.f16 = 1, a.have_D = true;
+        a.o = a.dq = a.pack = base, a.q = a.kc = a.vc = a.dout = base;
+        a.ld_dq = 3 * a.H, a.dq_seq = 3 * a.H, a.pack_l = a.l;
+        a.lse = a.D = a.dk = a.dv = a.ws = (float*)base;
+        a.ws_elems = 8 * (16384l * 128 + 2 * 16384);
+        a.pd = (uint16_t*)base, a.pd_elems = (long)heads * 4096 * 1024;
+        least = 0;
+        if (attn_bwd(DT_BF16, a, nullptr) != hipSuccess) ++bad;
+        kv_split += least > 0;
+        if (least > 0 && least < 256 && ++bad <= 40)
+          std::printf("dQ: %d heads, %d queries, %d keys in splits of %d\n", heads, n, r, least);
+      }
+  std::printf("column sums in chunks %d, dQ launches split %d\n", chunked, kv_split);
   if (bad) std::printf("FAILED %d\n", bad);
   return bad ? 1 : 0;
 }

@@ -1,8 +1,9 @@
-"""The scratch by which tp_slice_forward_static admits a slice covers the split plan
+"""How launches are split, on the CPU.  The scratch by which tp_slice_forward_static admits a slice covers the split plan
 that its kernels then follow, and an admitted plan stays within the static array: every
 forward product of widths 64 to 16384 and slices of 1 to 4096 rows, in bf16 and fp32,
 planned and "launched" on the CPU by tests/native/plan_driver.cpp, whose stand-ins for
-the HIP runtime record what a launch is given.  Which slices are admitted is pinned by
+the HIP runtime record what a launch is given.  The same driver checks the least work
+of a part of a split column sum or dQ launch (256 rows or keys).  Which slices are admitted is pinned by
 a table of answers."""
 import os
 import subprocess
