@@ -336,7 +336,13 @@ const char *tp_status_string(tp_status status);
  * the counters.  Returns the number of classes written (<= cap), or -1 when
  * the stream or an event could not be read (events recorded under stream
  * capture cannot be): the pending timings are then dropped and the counters
- * reset.  Launches captured into a graph are not timed by this mechanism. */
+ * reset.  Launches captured into a graph are not timed by this mechanism.
+ * The class of a launch is that of its main work: a LayerNorm (or the backward
+ * attention's row sums of dO * O) that runs in the reduction of a split product
+ * counts with that product, time and bytes, and not under "layernorm"; the
+ * LayerNorm-parameter gradients are column sums, with the bias gradients under
+ * "misc"; the four weight-gradient products of a layer may be one launch of
+ * "gemm_bwd_dw_tn". */
 typedef struct {
   char name[48];
   int64_t launches;

@@ -292,6 +292,11 @@ hipError_t run_gemm(tp_stage* S, int cls, GemmArgs g) {
                 [&] { return gemm(S->dt, g, S->stream); });
 }
 
+// Bytes of work that the launch just made does on the way.
+void add_bytes(tp_stage* S, double bytes) {
+  if (S->timing && !S->pending.empty()) S->pending.back().bytes += bytes;
+}
+
 // The product g, then the LayerNorm nm over its output rows (FWD; BWD: the product is
 // the LayerNorm's output gradient): in the product's split reduction where there is
 // one, else as a launch of its own.
@@ -299,9 +304,11 @@ hipError_t run_gemm_norm(tp_stage* S, int cls, GemmArgs g, const RowNorm& nm) {
   bool done = false;
   g.norm = &nm, g.norm_done = &done;
   const hipError_t e = run_gemm(S, cls, g);
-  if (e != hipSuccess || done) return e;
   const int H = S->H, n = g.M;
   const double nb = (double)n * H * S->esz;
+  // timed with the product, whose output rows it does not read back
+  if (done) add_bytes(S, (nm.bwd ? 3 : 1) * nb);
+  if (e != hipSuccess || done) return e;
   if (nm.bwd)
     return launch(S, K_NORM, 0, 4 * nb, [&] {
       return ln_bwd(S->dt, n, H, g.C, nm.x, nm.x_f32, nm.mean, nm.rstd, nm.g, nm.resid,
@@ -543,6 +550,7 @@ tp_status backward_impl(tp_stage* S, int l, int r, const void* dy, void* dx) {
     rd.d = S->d, rd.heads = S->heads, rd.Lmax = S->L, rd.l = l, rd.bs = S->bsz;
     if (mx) g.dot = &rd, g.dot_done = &have_D;
     TRY(run_gemm(S, K_GEMM_DX, g));
+    if (have_D) add_bytes(S, (double)n * A * e);
     // attention backward: dq rows, dK/dV into the fp32 buffer for keys [0, r)
     AttnArgs a;
     a.l = l, a.r = r, a.H = A, a.heads = S->heads, a.d = S->d, a.Lmax = S->L;
@@ -561,9 +569,11 @@ tp_status backward_impl(tp_stage* S, int l, int r, const void* dy, void* dx) {
     a.dkv_init = first ? 0 : r;
     a.pack_l = l, a.pack = a.dq;
     const double pairs = ((double)ntok * l + (double)ntok * (ntok + 1) / 2) * S->bsz;
-    TRY(launch(S, K_ATTN_BWD, 8.0 * A * pairs,
-               ((4.0 * ntok + 2.0 * r) * A * e + 16.0 * r * A) * S->bsz,
-               [&] { return attn_bwd(dt, a, st); }));
+    // q, dO, dq and (for D) o rows, K and V; dK and dV: fp32 sums read unless this is
+    // the first slice and written for keys < l, the slice's own keys leave as dqkv rows
+    const double bytes = ((have_D ? 3.0 : 4.0) * ntok + 2.0 * r + 2.0 * ntok) * A * e +
+                         ((first ? 0.0 : 8.0 * r) + 8.0 * l) * A;
+    TRY(launch(S, K_ATTN_BWD, 8.0 * A * pairs, bytes * S->bsz, [&] { return attn_bwd(dt, a, st); }));
     // QKV backward: du = [dq dk dv] W_qkv
     g = nn(n, H, 3 * A, rowp(B.dqkv, lr, 3 * A, e), 3 * A, P.w_qkv);
     g.C = du, g.ldc = H;
