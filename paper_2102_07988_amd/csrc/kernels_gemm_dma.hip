@@ -58,12 +58,11 @@ __device__ inline int swz_kc(int r) {
 // between bank 0 and bank 32, so XOR 4 on rows 2 and 3 of each 4 suffices and
 // keeps the 24 chunks of a row within range.
 // Rows of 128 bytes (R = 64) alternate between bank 0 and bank 32 too and take the
-// same XOR; the 4 rows of a read of 64-byte rows (R = 32) are contiguous.
+// same XOR.
 template <int R>
 __device__ inline int swz_mc(int k) {
-  static_assert(R % 128 == 0 || R == 192 || R == 64 || R == 32, "no transposing-read swizzle");
-  if constexpr (R == 32) return 0;
-  else if constexpr (R == 192 || R == 64) return ((k >> 1) & 1) << 2;
+  static_assert(R % 128 == 0 || R == 192 || R == 64, "no transposing-read swizzle");
+  if constexpr (R == 192 || R == 64) return ((k >> 1) & 1) << 2;
   else return (k & 3) << 2;
 }
 
@@ -650,6 +649,21 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK) void gemm_dma_kernel(ARGS arg
   }
 }
 
+// Raises a kernel's dynamic-LDS limit, once per kernel and device (bit d of a
+// per-kernel mask; devices past 31 set it on every launch).
+template <auto* FN>
+hipError_t raise_lds(size_t lds) {
+  static std::atomic<uint32_t> done{0};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) dev = 32;
+  const uint32_t bit = dev < 32 ? 1u << dev : 0u;
+  if (bit && (done.load(std::memory_order_acquire) & bit)) return hipSuccess;
+  const hipError_t e = hipFuncSetAttribute((const void*)FN,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e == hipSuccess) done.fetch_or(bit, std::memory_order_release);
+  return e;
+}
+
 template <int BM, int BN, int BK, int WGM, int WGN, int WGK, bool A_KC, bool B_KC, int STAGES,
           int SB, bool SPLIT, bool F16, bool TAIL>
 hipError_t launch_dma(const GemmArgs& a, hipStream_t s) {
@@ -662,22 +676,12 @@ hipError_t launch_dma(const GemmArgs& a, hipStream_t s) {
         (cdiv(cdiv(a.M, BM), TileWalk::SM) * cdiv(cdiv(a.N, BN), TileWalk::SN) + 7) / 8;
     grid = dim3(rounds * 8 * WALK_PER_XCD, 1, 1);
   }
-  // the dynamic-LDS limit is raised once per kernel and device (bit d of a
-  // per-kernel mask; devices past 31 set it on every launch)
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) dev = 32;
 #define TP_LAUNCH(E)                                                                         \
   do {                                                                                       \
-    auto* fn = gemm_dma_kernel<BM, BN, BK, WGM, WGN, WGK, A_KC, B_KC, E, SPLIT, STAGES, SB, F16, TAIL, \
-                               GemmArgs>;                                                  \
-    static std::atomic<uint32_t> attr_set{0};                                                \
-    const uint32_t bit = dev < 32 ? 1u << dev : 0u;                                          \
-    if (!bit || !(attr_set.load(std::memory_order_acquire) & bit)) {                         \
-      hipError_t e = hipFuncSetAttribute((const void*)fn,                                    \
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
-      if (e != hipSuccess) return e;                                                         \
-      attr_set.fetch_or(bit, std::memory_order_release);                                     \
-    }                                                                                        \
+    constexpr auto* fn = &gemm_dma_kernel<BM, BN, BK, WGM, WGN, WGK, A_KC, B_KC, E, SPLIT,   \
+                                          STAGES, SB, F16, TAIL, GemmArgs>;                  \
+    const hipError_t e = raise_lds<fn>(lds);                                                 \
+    if (e != hipSuccess) return e;                                                           \
     fn<<<grid, NTH, lds, s>>>(a);                                                            \
   } while (0)
   if constexpr (SPLIT) {
@@ -1040,10 +1044,9 @@ hipError_t launch_group(GemmGroup& g, hipStream_t s) {
     g.first[p + 1] = g.first[p] + (g.walk ? std::min(up, side) : tm * tn);
   }
   const int n = g.first[g.count], blocks = g.walk ? cdiv(n, 8) * 8 * WALK_PER_XCD : n;
-  auto* fn = gemm_dma_kernel<BM, BN, 64, WGM, WGN, 1, false, false, EPI_ACC_F32, false, STAGES, STAGES,
-                             false, TAIL, GemmGroup>;
-  const hipError_t e = hipFuncSetAttribute((const void*)fn,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  constexpr auto* fn = &gemm_dma_kernel<BM, BN, 64, WGM, WGN, 1, false, false, EPI_ACC_F32, false,
+                                        STAGES, STAGES, false, TAIL, GemmGroup>;
+  const hipError_t e = raise_lds<fn>(lds);
   if (e != hipSuccess) return e;
   fn<<<blocks, NTH, lds, s>>>(g);
   return hipGetLastError();

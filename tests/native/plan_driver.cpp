@@ -7,7 +7,8 @@
 // Prints one line per product whose launch takes more scratch than the admission said
 // or writes past the array that the admission grants, and "products N, split S".
 // Also the least work of a part: column sums over rows in chunks of at least 256 rows,
-// the streaming dQ kernel in key splits of at least 256 keys.
+// the streaming dQ kernel in key splits of at least 256 keys; and a GEMM kernel's
+// attributes are set by its first launch alone.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -18,8 +19,8 @@
 
 namespace {
 long recorded = 0;  // most fp32 partial sums among the launches since it was cleared
-int launches = 0;
-enum { GEMM, COLSUM, ATTN } kind = GEMM;  // what the launches' first argument is
+int launches = 0, attribute_calls = 0;
+enum { GEMM, COLSUM, ATTN, GROUP } kind = GEMM;  // what the launches' first argument is
 int least = 0;                            // rows of a chunk, keys of a split (0: unsplit)
 dim3 grid_, block_;
 size_t lds_;
@@ -35,6 +36,7 @@ extern "C" hipError_t hipLaunchKernel(const void*, dim3 grid, dim3, void** args,
     least = j.chunks > 1 ? j.rows_per : 0;
     return hipSuccess;
   }
+  if (kind == GROUP) return hipSuccess;
   if (kind == ATTN) {
     const tp::AttnArgs& a = *(const tp::AttnArgs*)args[0];
     if (a.nsplit > 1) least = a.kv_chunk;
@@ -51,7 +53,10 @@ extern "C" hipError_t hipLaunchKernel(const void*, dim3 grid, dim3, void** args,
   ++launches;
   return hipSuccess;
 }
-extern "C" hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
+extern "C" hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) {
+  ++attribute_calls;
+  return hipSuccess;
+}
 extern "C" hipError_t hipGetDevice(int* d) { return *d = 0, hipSuccess; }
 extern "C" hipError_t hipGetLastError() { return hipSuccess; }
 extern "C" hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t lds, hipStream_t s) {
@@ -146,6 +151,20 @@ int main() {
         if (least > 0 && least < 256 && ++bad <= 40)
           std::printf("dQ: %d heads, %d queries, %d keys in splits of %d\n", heads, n, r, least);
       }
+  kind = GROUP;
+  for (int H : {1024, 2048, 12288})
+    for (int pass = 0; pass < 2; ++pass) {
+      GemmArgs g[4];
+      for (int i = 0; i < 4; ++i) {
+        g[i].M = i == 1 ? 4 * H : i == 3 ? 3 * H : H, g[i].N = i == 0 ? 4 * H : H, g[i].K = 256;
+        g[i].A = g[i].B = base, g[i].sam = g[i].sbn = 1, g[i].sak = g[i].M, g[i].sbk = g[i].N;
+        g[i].epi = EPI_ACC_F32, g[i].C = base, g[i].ldc = g[i].N;
+      }
+      attribute_calls = 0;
+      const bool run = gemm_dw_group(g, 4, nullptr) == hipSuccess;
+      if (pass && run && attribute_calls && ++bad)
+        std::printf("grouped products, H %d: %d attribute calls in the second launch\n", H, attribute_calls);
+    }
   std::printf("column sums in chunks %d, dQ launches split %d\n", chunked, kv_split);
   if (bad) std::printf("FAILED %d\n", bad);
   return bad ? 1 : 0;
