@@ -1,5 +1,7 @@
-// Prefix-causal attention of a token slice on the CDNA4 matrix cores (bf16
-// operands, fp32 accumulation, v_mfma_f32_32x32x16_bf16), head width 64 or 128.
+// Prefix-causal attention of a token slice on the CDNA4 matrix cores (fp32
+// accumulation, v_mfma_f32_32x32x16_f16 / _bf16), head width 64 or 128: the
+// mixed-precision path of a bf16 stage.  q, k, the forward's v, its softmax weights
+// and the backward's dS are fp16, the backward's v and the gradients bf16.
 //
 // Queries t in [l, r) attend keys s <= t of the per-layer cache [0, r) (Eq. 2
 // with every earlier slice's keys/values cached).
@@ -18,8 +20,9 @@
 //  forward  : S^T = K Q^T (lane = one query: the online softmax is lane-local
 //             plus one exchange with lane ^ 32), O^T += V^T P^T.
 //  dK/dV    : one block of 32 keys per wave; S = Q K^T and dP = dO V^T (lane =
-//             one key), dV += P^T dO, dK += dS^T Q; results are added to the
-//             fp32 dK/dV buffer (each element owned by one lane: no atomics).
+//             one key), dV += P^T dO, dK += dS^T Q; results are stored in or
+//             added to the fp32 dK/dV buffer, or leave as final bf16 rows (each
+//             element owned by one lane: no atomics).
 //  dQ       : one block of 32 queries per wave; S^T = K Q^T, dP^T = V dO^T,
 //             dQ^T += K^T dS^T.
 //  stored dS: the dK kernel also writes dS of every (key, query) block it
@@ -49,14 +52,9 @@ __device__ inline f32x16_t mfma(u32x4 a, u32x4 b, f32x16_t c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a),
                                                  __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
-// fp16 operands (F16) or bf16
-template <bool F16>
-__device__ inline f32x16_t mfma_t(u32x4 a, u32x4 b, f32x16_t c) {
-  if constexpr (F16)
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, a),
-                                                  __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
-  else
-    return mfma(a, b, c);
+__device__ inline f32x16_t mfma_f16(u32x4 a, u32x4 b, f32x16_t c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, a),
+                                                __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
 }
 
 __device__ inline f32x16_t zero16() {
@@ -115,20 +113,15 @@ __device__ inline uint32_t pack_f16x2(float lo, float hi) {
   typedef float f32x2_t __attribute__((ext_vector_type(2)));
   return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){lo, hi}, f16x2_t));
 }
-// 8 accumulator values as an fp16 (F16) or bf16 operand.
-template <bool F16>
-__device__ inline u32x4 acc_half(const f32x16_t& x, int ks) {
-  if constexpr (F16) {
-    u32x4 u;
-    const int o = 8 * ks;
-    u.x = pack_f16x2(x[o + 0], x[o + 1]);
-    u.y = pack_f16x2(x[o + 2], x[o + 3]);
-    u.z = pack_f16x2(x[o + 4], x[o + 5]);
-    u.w = pack_f16x2(x[o + 6], x[o + 7]);
-    return u;
-  } else {
-    return acc_half_bf16(x, ks);
-  }
+// 8 accumulator values as an fp16 operand.
+__device__ inline u32x4 acc_half_f16(const f32x16_t& x, int ks) {
+  u32x4 u;
+  const int o = 8 * ks;
+  u.x = pack_f16x2(x[o + 0], x[o + 1]);
+  u.y = pack_f16x2(x[o + 2], x[o + 3]);
+  u.z = pack_f16x2(x[o + 4], x[o + 5]);
+  u.w = pack_f16x2(x[o + 6], x[o + 7]);
+  return u;
 }
 
 // Tile of rows x D bf16 in LDS, rows of 2D bytes whose 16-byte chunks are
@@ -268,8 +261,7 @@ __device__ inline u32x4 mask_keys(u32x4 x, int r0, int G, int r) {
 // other's matrix products
 // SPLIT: this block takes only split blockIdx.z % nsplit of the keys and
 // leaves the unnormalised output with its running maximum and sum.
-// F16: q, k and v are fp16 (scores and P V on fp16 operands), else bf16.
-template <int D, int NW, bool SPLIT, bool F16>
+template <int D, int NW, bool SPLIT>
 __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_mfma(AttnArgs a0) {
   const AttnArgs a = attn_seq_view<uint16_t>(a0);
   const int zsp = SPLIT ? blockIdx.z % a.nsplit : 0;
@@ -341,9 +333,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_mfma(AttnArgs a0) {
           lgkm_wait(kf[0]);
 #pragma unroll
           for (int kk = 1; kk < KS; ++kk) lgkm_tie(kf[kk]);
-          s = mfma_t<F16>(kf[0], qf[0], zero16());
+          s = mfma_f16(kf[0], qf[0], zero16());
 #pragma unroll
-          for (int kk = 1; kk < KS; ++kk) s = mfma_t<F16>(kf[kk], qf[kk], s);
+          for (int kk = 1; kk < KS; ++kk) s = mfma_f16(kf[kk], qf[kk], s);
         }
         // keys of a sub-block that ends at or before the wave's first query
         // need no mask (all are <= every query of the wave and < r)
@@ -390,7 +382,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_mfma(AttnArgs a0) {
         if (kbase + 32 * sb >= kend_w) break;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
-          const u32x4 pb = acc_half<F16>(p[sb], ks);
+          const u32x4 pb = acc_half_f16(p[sb], ks);
           u32x4 vf[JB];
 #pragma unroll
           for (int j = 0; j < JB; ++j) vf[j] = T::col8(Vt, 32 * sb + 16 * ks, 32 * j, lane);
@@ -398,7 +390,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_mfma(AttnArgs a0) {
 #pragma unroll
           for (int j = 1; j < JB; ++j) lgkm_tie(vf[j]);
 #pragma unroll
-          for (int j = 0; j < JB; ++j) o[j] = mfma_t<F16>(vf[j], pb, o[j]);
+          for (int j = 0; j < JB; ++j) o[j] = mfma_f16(vf[j], pb, o[j]);
         }
       }
     }
@@ -527,7 +519,7 @@ __device__ inline void out_rows(float* buf, const f32x16_t (&acc)[JB], float mul
 // head; query block qb (queries l + 32 qb ...) holds r rows of 32 values, row
 // = key, at qb * r * 32 + key * 32, so a wave's stores of one block fill whole
 // contiguous lines and a reader's tile of consecutive keys is one contiguous
-// piece.  Values fp16 (F16) or bf16, as the dK product rounds them, in operand
+// piece.  Values fp16, as the dK product rounds them, in operand
 // order: query 16 h + 4 G + e + 8 u (e < 4) at column 16 h + 8 G + 4 u + e,
 // i.e. bits 2 and 3 of the query index swapped, so each lane stores the 8
 // values of a reduction half with one 16-byte store.  A (32-key, 32-query) block is written when its first key is below r
@@ -535,9 +527,7 @@ __device__ inline void out_rows(float* buf, const f32x16_t (&acc)[JB], float mul
 // condition under which the dQ kernel reads it.
 // ST query tiles form the LDS ring: tile qb + ST - 1 is requested while tile
 // qb is multiplied.
-// F16: q and k are fp16 (scores on fp16 operands; the dK kernel's dS product
-// on fp16 dS); v and the gradients stay bf16.
-template <int D, int NW, int MODE, int ST, bool F16>
+template <int D, int NW, int MODE, int ST>
 __device__ inline void dkdv_body(const AttnArgs& a0, int seq) {
   static_assert(MODE >= 1 && MODE <= 3, "dV (1), dK (2), dK storing dS (3)");
   const AttnArgs a = attn_seq_view<uint16_t>(a0, seq);
@@ -644,7 +634,7 @@ __device__ inline void dkdv_body(const AttnArgs& a0, int seq) {
 #pragma unroll
         for (int b = 0; b < 4; ++b) lgkm_tie(lq[b]);
 #pragma unroll
-        for (int kk = 0; kk < KS; ++kk) s = mfma_t<F16>(qa[kk], kf[kk], s);
+        for (int kk = 0; kk < KS; ++kk) s = mfma_f16(qa[kk], kf[kk], s);
       }
       // s[v]: query row qi = 8 (v / 4) + 4 G + v % 4 of the block, key s_me.
       // P first, so the lse values are dead before the dP product.
@@ -713,7 +703,7 @@ __device__ inline void dkdv_body(const AttnArgs& a0, int seq) {
           for (int j = 0; j < JB; ++j) dv[j] = mfma(pb, ob[j], dv[j]);
         }
         if constexpr (DO_K) {
-          const u32x4 db = acc_half<F16>(ds, ks);
+          const u32x4 db = acc_half_f16(ds, ks);
           if constexpr (STORE) {
             if (s_me < a.r) *(u32x4*)(a.dst + prow + (long)(i0 >> 5) * a.r * 32 + 16 * ks + 8 * G) = db;
           }
@@ -724,7 +714,7 @@ __device__ inline void dkdv_body(const AttnArgs& a0, int seq) {
 #pragma unroll
           for (int j = 1; j < JB; ++j) lgkm_tie(qb2[j]);
 #pragma unroll
-          for (int j = 0; j < JB; ++j) dk[j] = mfma_t<F16>(db, qb2[j], dk[j]);
+          for (int j = 0; j < JB; ++j) dk[j] = mfma_f16(db, qb2[j], dk[j]);
         }
       }
     }
@@ -744,21 +734,20 @@ __device__ inline void dkdv_body(const AttnArgs& a0, int seq) {
 // the other, 31 us together; short prefixes, 4-wave blocks, 30 -> 22 us).  With enough
 // blocks it still saves a part-empty last round (96 heads: 123 -> 114 us; 16 heads and
 // 8k keys: 114 -> 105 us).
-template <int D, int NW, int MK, int STK, int STV, bool F16>
+template <int D, int NW, int MK, int STK, int STV>
 __global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dkdv_mfma(AttnArgs a) {
   const int seq = blockIdx.z % a.bs;
   if ((int)blockIdx.z < a.bs)
-    dkdv_body<D, NW, MK, STK, F16>(a, seq);
+    dkdv_body<D, NW, MK, STK>(a, seq);
   else
-    dkdv_body<D, NW, 1, STV, F16>(a, seq);
+    dkdv_body<D, NW, 1, STV>(a, seq);
 }
 
 // ------------------------------------------------------------------- dQ
 
 // SPLIT: this block takes only split blockIdx.z % nsplit of the keys and
 // leaves its unscaled fp32 dQ partial.
-// F16: q and k are fp16 (scores and the dS K product on fp16 operands).
-template <int D, int NW, bool SPLIT, bool F16>
+template <int D, int NW, bool SPLIT>
 __global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dq_mfma(AttnArgs a0) {
   const AttnArgs a = attn_seq_view<uint16_t>(a0);
   const int zsp = SPLIT ? blockIdx.z % a.nsplit : 0;
@@ -827,7 +816,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dq_mfma(AttnArgs a0) {
 #pragma unroll
         for (int kk = 1; kk < KS; ++kk) lgkm_tie(ka[kk]);
 #pragma unroll
-        for (int kk = 0; kk < KS; ++kk) s = mfma_t<F16>(ka[kk], qf[kk], s);
+        for (int kk = 0; kk < KS; ++kk) s = mfma_f16(ka[kk], qf[kk], s);
       }
       {
         u32x4 va[KS];
@@ -857,7 +846,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dq_mfma(AttnArgs a0) {
       }
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
-        const u32x4 db = acc_half<F16>(ds, ks);
+        const u32x4 db = acc_half_f16(ds, ks);
         u32x4 kt[JB];
 #pragma unroll
         for (int j = 0; j < JB; ++j) kt[j] = T::col8(Kt, 32 * sb + 16 * ks, 32 * j, lane);
@@ -865,7 +854,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dq_mfma(AttnArgs a0) {
 #pragma unroll
         for (int j = 1; j < JB; ++j) lgkm_tie(kt[j]);
 #pragma unroll
-        for (int j = 0; j < JB; ++j) dq[j] = mfma_t<F16>(kt[j], db, dq[j]);
+        for (int j = 0; j < JB; ++j) dq[j] = mfma_f16(kt[j], db, dq[j]);
       }
     }
   }
@@ -900,7 +889,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dq_mfma(AttnArgs a0) {
 // Rows of keys >= r (repeats in the last tile) are zeroed in the dS operand.
 // SPLIT: this block takes only split blockIdx.z % nsplit of the keys and leaves its
 // unscaled fp32 dQ partial.
-template <int D, int NW, int QH, int ST, bool SPLIT, bool F16>
+template <int D, int NW, int QH, int ST, bool SPLIT>
 __global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dq_stream(AttnArgs a0) {
   const AttnArgs a = attn_seq_view<uint16_t>(a0);
   const int zsp = SPLIT ? blockIdx.z % a.nsplit : 0, seq = blockIdx.z / a.nsplit;
@@ -981,7 +970,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bwd_dq_stream(AttnArgs a0) {
         for (int qh = 0; qh < QH; ++qh)
           if (act[qh]) {
 #pragma unroll
-            for (int j = 0; j < JB; ++j) dq[qh][j] = mfma_t<F16>(kt[j], db[qh], dq[qh][j]);
+            for (int j = 0; j < JB; ++j) dq[qh][j] = mfma_f16(kt[j], db[qh], dq[qh][j]);
           }
       }
     }
@@ -1136,7 +1125,7 @@ hipError_t set_lds(K* fn, size_t bytes) {
                              (int)bytes);
 }
 
-template <int D, bool F16>
+template <int D>
 hipError_t fwd_d(const AttnArgs& a, hipStream_t s) {
   const int n = a.r - a.l;
   constexpr size_t lds = 2 * 2 * 64 * D * 2;
@@ -1147,15 +1136,15 @@ hipError_t fwd_d(const AttnArgs& a, hipStream_t s) {
     return hipSuccess;
   }
   if (b.nsplit == 1) {
-    hipError_t e = set_lds(attn_fwd_mfma<D, NWF, false, F16>, lds);
+    hipError_t e = set_lds(attn_fwd_mfma<D, NWF, false>, lds);
     if (e != hipSuccess) return e;
-    attn_fwd_mfma<D, NWF, false, F16>
+    attn_fwd_mfma<D, NWF, false>
         <<<dim3(cdiv(n, 32 * NWF), a.heads, a.bs), 64 * NWF, lds, s>>>(a);
     return hipGetLastError();
   }
-  hipError_t e = set_lds(attn_fwd_mfma<D, NWF, true, F16>, lds);
+  hipError_t e = set_lds(attn_fwd_mfma<D, NWF, true>, lds);
   if (e != hipSuccess) return e;
-  attn_fwd_mfma<D, NWF, true, F16>
+  attn_fwd_mfma<D, NWF, true>
       <<<dim3(cdiv(n, 32 * NWF), a.heads, a.bs * b.nsplit), 64 * NWF, lds, s>>>(b);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -1163,27 +1152,23 @@ hipError_t fwd_d(const AttnArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int D, bool F16>
+template <int D>
 hipError_t dq_d(const AttnArgs& a, hipStream_t s) {
   const int n = a.r - a.l;
   hipError_t e;
   constexpr size_t lds_q = 2 * 2 * 64 * D * 2;
   AttnArgs b = a;
   plan_split(b, false);
-  if (a.need) {
-    *a.need = b.nsplit > 1 ? (long)b.nsplit * n * a.bs * a.H : 0;
-    return hipSuccess;
-  }
   if (b.nsplit == 1) {
-    e = set_lds(attn_bwd_dq_mfma<D, NWF, false, F16>, lds_q);
+    e = set_lds(attn_bwd_dq_mfma<D, NWF, false>, lds_q);
     if (e != hipSuccess) return e;
-    attn_bwd_dq_mfma<D, NWF, false, F16>
+    attn_bwd_dq_mfma<D, NWF, false>
         <<<dim3(cdiv(n, 32 * NWF), a.heads, a.bs), 64 * NWF, lds_q, s>>>(a);
     return hipGetLastError();
   }
-  e = set_lds(attn_bwd_dq_mfma<D, NWF, true, F16>, lds_q);
+  e = set_lds(attn_bwd_dq_mfma<D, NWF, true>, lds_q);
   if (e != hipSuccess) return e;
-  attn_bwd_dq_mfma<D, NWF, true, F16>
+  attn_bwd_dq_mfma<D, NWF, true>
       <<<dim3(cdiv(n, 32 * NWF), a.heads, a.bs * b.nsplit), 64 * NWF, lds_q, s>>>(b);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -1211,39 +1196,39 @@ void plan_stream_split(AttnArgs& a) {
   a.nsplit = cdiv(a.r, a.kv_chunk);
 }
 
-template <int D, int NW, int MK, int STK, int STV, bool F16>
+template <int D, int NW, int MK, int STK, int STV>
 hipError_t launch_dkdv(const AttnArgs& a, hipStream_t s) {
   constexpr size_t lds_k = STK * (2 * 32 * D + NW * 128) * 2 + 32 * NW * D * 2;
   constexpr size_t lds_v = STV * (2 * 32 * D + NW * 128) * 2;
   constexpr size_t lds = lds_k > lds_v ? lds_k : lds_v;
-  hipError_t e = set_lds(attn_bwd_dkdv_mfma<D, NW, MK, STK, STV, F16>, lds);
+  hipError_t e = set_lds(attn_bwd_dkdv_mfma<D, NW, MK, STK, STV>, lds);
   if (e != hipSuccess) return e;
-  attn_bwd_dkdv_mfma<D, NW, MK, STK, STV, F16>
+  attn_bwd_dkdv_mfma<D, NW, MK, STK, STV>
       <<<dim3(cdiv(a.r, 32 * NW), a.heads, 2 * a.bs), 64 * NW, lds, s>>>(a);
   return hipGetLastError();
 }
 
-// Block shapes of the dK / dV kernel: with head width 128 8 waves (256 keys) over
-// 4-tile rings (137 KB, the dK blocks' V rows included: one block per CU), with 64 4
-// waves over rings of 2 (dK) and 4 (dV) tiles.
-template <int D, int MK, bool F16>
+// Block shapes of the dK / dV kernel that stores dS: with head width 128 8 waves (256
+// keys) over 4-tile rings (137 KB, the dK blocks' V rows included: one block per CU),
+// with 64 4 waves over rings of 2 (dK) and 4 (dV) tiles.
+template <int D>
 hipError_t dkdv_d(const AttnArgs& a, hipStream_t s) {
-  return launch_dkdv<D, D == 128 ? 8 : 4, MK, D == 128 ? 4 : 2, 4, F16>(a, s);
+  return launch_dkdv<D, D == 128 ? 8 : 4, 3, D == 128 ? 4 : 2, 4>(a, s);
 }
 
 // Backward with stored dS: over query chunks of at most cq rows (a multiple of 256)
 // whose dS planes fit the scratch, the dK blocks (MODE 3) write the planes that the
 // streaming dQ kernel then reads (the rows' D = rowsum(dO * O) is already computed
 // for the whole slice).
-template <int D, bool F16>
+template <int D>
 hipError_t bwd_stored(const AttnArgs& a, hipStream_t s, long cq) {
   // dQ: 256 queries per block (8 waves) when that fills the CUs, else 128
   constexpr int STQ = 2;
   constexpr size_t lds_q4 = STQ * (64 * D + 64 * 128) * 2, lds_q8 = STQ * (64 * D + 64 * 256) * 2;
   const bool q8 = (long)cdiv(std::min<long>(a.r - a.l, cq), 256) * a.heads * a.bs >= 128;
-  hipError_t e = q8 ? set_lds(attn_bwd_dq_stream<D, 8, 1, STQ, false, F16>, lds_q8)
-                    : set_lds(attn_bwd_dq_stream<D, 4, 1, STQ, false, F16>, lds_q4);
-  if (e == hipSuccess) e = set_lds(attn_bwd_dq_stream<D, 4, 1, STQ, true, F16>, lds_q4);
+  hipError_t e = q8 ? set_lds(attn_bwd_dq_stream<D, 8, 1, STQ, false>, lds_q8)
+                    : set_lds(attn_bwd_dq_stream<D, 4, 1, STQ, false>, lds_q4);
+  if (e == hipSuccess) e = set_lds(attn_bwd_dq_stream<D, 4, 1, STQ, true>, lds_q4);
   if (e != hipSuccess) return e;
   const int n = a.r - a.l;
   for (int c0 = 0; c0 < n; c0 += (int)cq) {
@@ -1259,20 +1244,20 @@ hipError_t bwd_stored(const AttnArgs& a, hipStream_t s, long cq) {
     // an earlier chunk has left sums for every key it saw; only the last one's are final
     if (c0 > 0) b.dkv_init = std::max(a.dkv_init, a.l + c0);
     if (c1 < n) b.pack_l = b.r;
-    e = dkdv_d<D, 3, F16>(b, s);
+    e = dkdv_d<D>(b, s);
     if (e != hipSuccess) return e;
     if (!q8) plan_stream_split(b);
     if (b.nsplit > 1) {
-      attn_bwd_dq_stream<D, 4, 1, STQ, true, F16>
+      attn_bwd_dq_stream<D, 4, 1, STQ, true>
           <<<dim3(cdiv(c1 - c0, 128), a.heads, a.bs * b.nsplit), 256, lds_q4, s>>>(b);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
       attn_dq_combine<<<cdiv((long)(c1 - c0) * a.bs * (a.H / 8), 256), 256, 0, s>>>(b);
     } else if (q8) {
-      attn_bwd_dq_stream<D, 8, 1, STQ, false, F16>
+      attn_bwd_dq_stream<D, 8, 1, STQ, false>
           <<<dim3(cdiv(c1 - c0, 256), a.heads, a.bs), 512, lds_q8, s>>>(b);
     } else {
-      attn_bwd_dq_stream<D, 4, 1, STQ, false, F16>
+      attn_bwd_dq_stream<D, 4, 1, STQ, false>
           <<<dim3(cdiv(c1 - c0, 128), a.heads, a.bs), 256, lds_q4, s>>>(b);
     }
     e = hipGetLastError();
@@ -1281,37 +1266,31 @@ hipError_t bwd_stored(const AttnArgs& a, hipStream_t s, long cq) {
   return hipSuccess;
 }
 
-template <int D, bool F16>
+template <int D>
 hipError_t bwd_d(const AttnArgs& a, hipStream_t s) {
   const int n = a.r - a.l;
-  if (a.need) return dq_d<D, F16>(a, s);  // only the dQ kernel takes split scratch
+  // few key blocks (few heads, short prefix): four-wave blocks over two-tile rings, so
+  // more blocks share the CUs
+  const bool few = (long)cdiv(a.r, 128) * a.heads * a.bs < 128;
+  // query rows per chunk whose dS planes (whole 256-query blocks) fit
+  const long cq = a.pd ? a.pd_elems / ((long)a.bs * a.heads * a.r) / 256 * 256 : 0;
+  if (!few && cq < 256) return hipErrorNotSupported;
   hipError_t e = hipSuccess;
   if (!a.have_D) {
     attn_bwd_rowdot<D><<<dim3(cdiv((long)n * a.heads, 4), 1, a.bs), 256, 0, s>>>(a);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  if ((long)cdiv(a.r, 128) * a.heads * a.bs < 128) {
-    // few key blocks (few heads, short prefix): four-wave blocks over two-tile
-    // rings, so more blocks share the CUs
-    e = launch_dkdv<D, 4, 2, 2, 2, F16>(a, s);
-    if (e != hipSuccess) return e;
-    return dq_d<D, F16>(a, s);
-  }
-  if (a.pd) {
-    // query rows per chunk whose dS planes (whole 256-query blocks) fit
-    const long cq = a.pd_elems / ((long)a.bs * a.heads * a.r) / 256 * 256;
-    if (cq >= 256) return bwd_stored<D, F16>(a, s, cq);
-  }
-  e = dkdv_d<D, 2, F16>(a, s);
+  if (!few) return bwd_stored<D>(a, s, cq);
+  e = launch_dkdv<D, 4, 2, 2, 2>(a, s);
   if (e != hipSuccess) return e;
-  return dq_d<D, F16>(a, s);
+  return dq_d<D>(a, s);
 }
 
 inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 bool covered(const AttnArgs& a) {
-  return (a.d == 64 || a.d == 128) && (a.H % 8) == 0 && (a.ld % 8) == 0 && al16(a.q) &&
+  return a.f16 && (a.d == 64 || a.d == 128) && (a.H % 8) == 0 && (a.ld % 8) == 0 && al16(a.q) &&
          al16(a.kc) && al16(a.vc);
 }
 
@@ -1319,15 +1298,13 @@ bool covered(const AttnArgs& a) {
 
 hipError_t attn_fwd_mfma_bf16(const AttnArgs& a, hipStream_t s) {
   if (!covered(a) || !al16(a.o)) return hipErrorNotSupported;
-  if (a.f16) return a.d == 128 ? fwd_d<128, true>(a, s) : fwd_d<64, true>(a, s);
-  return a.d == 128 ? fwd_d<128, false>(a, s) : fwd_d<64, false>(a, s);
+  return a.d == 128 ? fwd_d<128>(a, s) : fwd_d<64>(a, s);
 }
 
 hipError_t attn_bwd_mfma_bf16(const AttnArgs& a, hipStream_t s) {
   if (!covered(a) || !al16(a.dout) || !al16(a.dq) || (a.ld_dq % 8) || (a.dq_seq % 8))
     return hipErrorNotSupported;
-  if (a.f16) return a.d == 128 ? bwd_d<128, true>(a, s) : bwd_d<64, true>(a, s);
-  return a.d == 128 ? bwd_d<128, false>(a, s) : bwd_d<64, false>(a, s);
+  return a.d == 128 ? bwd_d<128>(a, s) : bwd_d<64>(a, s);
 }
 
 }  // namespace tp

@@ -172,9 +172,10 @@ struct AttnArgs {
   // elements (forward: with the running maxima and sums), 0 without a split.
   long* need = nullptr;
   // Backward scratch of pd_elems 16-bit elements for the stored dS planes
-  // (matrix-core path): the dK kernel writes dS and the dQ kernel streams it
-  // instead of recomputing the scores; slices whose planes do not fit run in
-  // query chunks.  Null: the recomputing dQ kernel.
+  // (mixed-precision path; room for 256 query rows of every head and key): the dK
+  // kernel writes dS and the dQ kernel streams it instead of recomputing the scores;
+  // slices whose planes do not fit run in query chunks.  Launches of few key blocks
+  // recompute and need none.
   uint16_t* pd = nullptr;
   long pd_elems = 0;
   // set by the launcher: the planes' base and their query columns

@@ -139,14 +139,16 @@ int main() {
         if ((r + 127) / 128 * heads < 128) continue;
         AttnArgs a;
         a.l = r - n, a.r = r, a.d = 128, a.heads = heads, a.H = a.ld = heads * 128;
-        a.Lmax = 4096, a.f16 = 1, a.have_D = true;
+        a.Lmax = r, a.f16 = 1, a.have_D = true;
         a.o = a.dq = a.pack = base, a.q = a.kc = a.vc = a.dout = base;
         a.ld_dq = 3 * a.H, a.dq_seq = 3 * a.H, a.pack_l = a.l;
         a.lse = a.D = a.dk = a.dv = a.ws = (float*)base;
         a.ws_elems = 8 * (16384l * 128 + 2 * 16384);
-        a.pd = (uint16_t*)base, a.pd_elems = (long)heads * 4096 * 1024;
+        // the stage's dS planes at the longest slice of the shortest stage that has it
+        a.pd = (uint16_t*)base, a.pd_elems = (long)heads * r * std::min(1024, (r + 255) / 256 * 256);
         least = 0;
-        if (attn_bwd(DT_BF16, a, nullptr) != hipSuccess) ++bad;
+        if (attn_bwd(DT_BF16, a, nullptr) != hipSuccess && ++bad <= 40)
+          std::printf("dQ: %d heads, %d queries, %d keys not taken\n", heads, n, r);
         kv_split += least > 0;
         if (least > 0 && least < 256 && ++bad <= 40)
           std::printf("dQ: %d heads, %d queries, %d keys in splits of %d\n", heads, n, r, least);
