@@ -84,7 +84,7 @@ typedef struct {
   int n_layers;   /* layers in this stage, >= 1 */
   int hidden;     /* H; FFN width is 4H */
   int heads;      /* a; head width d = H / a must be 16, 32, 64 or 128; H % 8 == 0, H <= 16384 */
-  int max_seq;    /* largest sequence length L the stage will see */
+  int max_seq;    /* largest sequence length L the stage will see, at most 20344 */
   int dtype;      /* tp_dtype */
   int wgrad_mode; /* tp_wgrad_mode */
   float ln_eps;   /* LayerNorm epsilon (1e-5 in the GPT-3 setting) */

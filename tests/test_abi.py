@@ -242,3 +242,12 @@ def test_static_forward_plans_on_the_host():
     assert f(h, 0, 257, X, Y) == tp.TP_ERR_INVALID
     assert f(h, 0, 8, None, Y) == tp.TP_ERR_INVALID
     tp.lib.tp_stage_destroy(h)
+
+
+def test_longest_sequence():
+    """20344 tokens are the longest sequence a stage accepts."""
+    for dtype, batch in (("bf16", 1), ("bf16", 64), ("fp32", 1)):
+        rc, h = _init(tp.make_config(1, 256, 2, 20344, dtype, batch=batch))
+        assert rc == tp.TP_OK
+        tp.lib.tp_stage_destroy(h)
+        assert _init(tp.make_config(1, 256, 2, 20345, dtype, batch=batch))[0] == tp.TP_ERR_UNSUPPORTED
