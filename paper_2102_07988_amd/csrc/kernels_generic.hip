@@ -106,6 +106,17 @@ __device__ inline void load8(const float* p, float* v) {
   const float4 a = ((const float4*)p)[0], b = ((const float4*)p)[1];
   v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w, v[4] = b.x, v[5] = b.y, v[6] = b.z, v[7] = b.w;
 }
+// Gain and offset parameters: 16-byte loads where the caller's tensors are aligned (AL),
+// else element by element.
+template <bool AL, typename T>
+__device__ inline void load8_param(const T* p, float* v) {
+  if constexpr (AL) {
+    load8(p, v);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = ld(p + e);
+  }
+}
 __device__ inline void store8(bf16* p, const float* v) {
   uint4 u;
   u.x = f32_to_bf16_bits(v[0]) | ((uint32_t)f32_to_bf16_bits(v[1]) << 16);
@@ -135,7 +146,7 @@ inline LnShape ln_shape(int H) {
 // T: stage dtype (gamma, beta, u); TX: type of the input rows x (fp32 for the
 // residual stream of a mixed-precision stage).  x_copy (fp32 when copy_f32, else
 // T) and u16 (fp16 copy of u) are optional.
-template <typename T, typename TX, int CPT>
+template <typename T, typename TX, int CPT, bool AL>
 __global__ __launch_bounds__(1024) void ln_fwd_kernel(int H, const TX* x, void* x_copy,
                                                       int copy_f32, const T* g, const T* b, T* u,
                                                       f16s* u16, float* mean, float* rstd,
@@ -149,8 +160,8 @@ __global__ __launch_bounds__(1024) void ln_fwd_kernel(int H, const TX* x, void* 
     const int ci = threadIdx.x + nt * c;
     if (ci < nc) {
       load8(xr + ci * 8, v[c]);
-      load8(g + ci * 8, gg[c]);
-      load8(b + ci * 8, bb[c]);
+      load8_param<AL>(g + ci * 8, gg[c]);
+      load8_param<AL>(b + ci * 8, bb[c]);
     }
   }
   float s = 0.f;
@@ -202,7 +213,7 @@ __device__ inline float2 block_sum2(float a, float b, float* red /* >= 32 floats
   return make_float2(sa, sb);
 }
 
-template <typename T, typename TX, int CPT>
+template <typename T, typename TX, int CPT, bool AL>
 __global__ __launch_bounds__(1024) void ln_bwd_kernel(int H, const T* du, const TX* x,
                                                       const float* mean, const float* rstd,
                                                       const T* g, const T* resid, T* resid_copy,
@@ -218,7 +229,7 @@ __global__ __launch_bounds__(1024) void ln_bwd_kernel(int H, const T* du, const 
       float gg[8];
       load8(x + (long)row * H + ci * 8, xh[c]);
       load8(du + (long)row * H + ci * 8, dg[c]);
-      load8(g + ci * 8, gg);
+      load8_param<AL>(g + ci * 8, gg);
       load8(resid + (long)row * H + ci * 8, r[c]);
 #pragma unroll
       for (int e = 0; e < 8; ++e) dg[c][e] *= gg[e];
@@ -362,10 +373,11 @@ hipError_t ln_fwd(int dtype, int n, int H, const void* x, int x_f32, void* x_cop
   clear_stale_error();
   if (n <= 0) return hipSuccess;
   const LnShape sh = ln_shape(H);
+  const bool al = !(((uintptr_t)g | (uintptr_t)b) & 15);
 #define TP_LN(TT, TX, C)                                                                   \
-  ln_fwd_kernel<TT, TX, C><<<n, sh.nt, 0, s>>>(H, (const TX*)x, x_copy, copy_f32,           \
-                                               (const TT*)g, (const TT*)b, (TT*)u,          \
-                                               (f16s*)u16, mean, rstd, eps)
+  (al ? ln_fwd_kernel<TT, TX, C, true> : ln_fwd_kernel<TT, TX, C, false>)                  \
+      <<<n, sh.nt, 0, s>>>(H, (const TX*)x, x_copy, copy_f32, (const TT*)g, (const TT*)b,   \
+                           (TT*)u, (f16s*)u16, mean, rstd, eps)
   if (dtype == DT_FP32) {
     if (sh.cpt == 1) TP_LN(float, float, 1); else TP_LN(float, float, 2);
   } else if (x_f32) {
@@ -383,10 +395,11 @@ hipError_t ln_bwd(int dtype, int n, int H, const void* du, const void* x, int x_
   clear_stale_error();
   if (n <= 0) return hipSuccess;
   const LnShape sh = ln_shape(H);
+  const bool al = !((uintptr_t)g & 15);
 #define TP_LN(TT, TX, C)                                                                   \
-  ln_bwd_kernel<TT, TX, C><<<n, sh.nt, 0, s>>>(H, (const TT*)du, (const TX*)x, mean, rstd,  \
-                                               (const TT*)g, (const TT*)resid,              \
-                                               (TT*)resid_copy, (TT*)dx)
+  (al ? ln_bwd_kernel<TT, TX, C, true> : ln_bwd_kernel<TT, TX, C, false>)                  \
+      <<<n, sh.nt, 0, s>>>(H, (const TT*)du, (const TX*)x, mean, rstd, (const TT*)g,        \
+                           (const TT*)resid, (TT*)resid_copy, (TT*)dx)
   if (dtype == DT_FP32) {
     if (sh.cpt == 1) TP_LN(float, float, 1); else TP_LN(float, float, 2);
   } else if (x_f32) {
