@@ -258,8 +258,11 @@ __device__ inline const GemmArgs& my_product(const GemmGroup& a, int i, int* loc
 // WGK: wave groups over the reduction: group wk of WGK takes its 1/WGK of every
 // k-tile's 16-value steps, and the groups' accumulators are added in LDS before the
 // epilogue.
+// KEEP: fp32 outputs stay in the caches (GemmArgs::keep); an instance of its own, as both
+// kinds of store in one epilogue cost the wide gradients 1 % (12288 wide, deferred, 2
+// slices: 7235 -> 7319 us).
 template <int BM, int BN, int BK, int WGM, int WGN, int WGK, bool A_KC, bool B_KC, int EPI,
-          bool SPLIT, int STAGES, int SB, bool F16, bool TAIL, typename ARGS>
+          bool SPLIT, int STAGES, int SB, bool F16, bool TAIL, typename ARGS, bool KEEP = false>
 __global__ __launch_bounds__(64 * WGM * WGN * WGK) void gemm_dma_kernel(ARGS args) {
   constexpr bool GROUP = std::is_same<ARGS, GemmGroup>::value;
   constexpr int NTH = 64 * WGM * WGN * WGK;
@@ -564,9 +567,6 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK) void gemm_dma_kernel(ARGS arg
     // while one is combined (a plain store with a.overwrite)
     constexpr int P = T < 4 ? T : 4;
     const bool add = !SPLIT && !a.overwrite;
-    // a gradient that is added to slice by slice is read again soon: up to 64 MB it is
-    // left in the caches (1024 wide, 4 slices, two sequences: 1327 -> 1312 us in all)
-    const bool keep = add && (long)a.M * a.N <= (16l << 20);
     float4 pre[P][4];
     if (add && full) {
 #pragma unroll
@@ -591,12 +591,12 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK) void gemm_dma_kernel(ARGS arg
             const float4 o = pre[t % P][q];
             x[q].x += o.x, x[q].y += o.y, x[q].z += o.z, x[q].w += o.w;
           }
-          if (SPLIT || keep) {
+          if constexpr (SPLIT || KEEP) {
             *(float4*)dst_of(t, q) = x[q];
           } else {
             // a stored fp32 weight gradient is not read again by this sequence's
-            // kernels: a non-temporal store keeps it from displacing their
-            // operands in the caches
+            // kernels, or not before the caches have moved on: a non-temporal store
+            // keeps it from displacing their operands
             const f32x4v v = {x[q].x, x[q].y, x[q].z, x[q].w};
             __builtin_nontemporal_store(v, (f32x4v*)dst_of(t, q));
           }
@@ -1028,8 +1028,10 @@ TileChoice choose_dw(const GemmArgs& a, double* us = nullptr) {
 }
 
 // One launch over the products of a group with tiles of BM x BN.
-template <int BM, int BN, int WGM, int WGN, int STAGES, bool TAIL>
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool TAIL, bool KEEP = false>
 hipError_t launch_group(GemmGroup& g, hipStream_t s) {
+  if constexpr (!KEEP)
+    if (g.g[0].keep) return launch_group<BM, BN, WGM, WGN, STAGES, TAIL, true>(g, s);
   constexpr int NTH = 64 * WGM * WGN;
   constexpr size_t lds = (size_t)STAGES * (BM + BN) * 64 * 2;
   long tiles = 0;
@@ -1045,7 +1047,7 @@ hipError_t launch_group(GemmGroup& g, hipStream_t s) {
   }
   const int n = g.first[g.count], blocks = g.walk ? cdiv(n, 8) * 8 * WALK_PER_XCD : n;
   constexpr auto* fn = &gemm_dma_kernel<BM, BN, 64, WGM, WGN, 1, false, false, EPI_ACC_F32, false,
-                                        STAGES, STAGES, false, TAIL, GemmGroup>;
+                                        STAGES, STAGES, false, TAIL, GemmGroup, KEEP>;
   const hipError_t e = raise_lds<fn>(lds);
   if (e != hipSuccess) return e;
   fn<<<blocks, NTH, lds, s>>>(g);

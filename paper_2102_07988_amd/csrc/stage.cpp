@@ -362,9 +362,16 @@ tp_status wgrad_gemms(tp_stage* S, int li, int l, int n) {
       tn(F, H, n, rowp(B.dz, l, F, e), F, rowp(B.u2, l, H, e), H, (float*)G.w_fc1),
       tn(H, A, n, rowp(B.dx1, l, H, e), H, rowp(B.o, l, A, e), A, (float*)G.w_o),
       tn(3 * A, H, n, rowp(B.dqkv, l, 3 * A, e), 3 * A, rowp(B.u, l, H, e), H, (float*)G.w_qkv)};
+  // Gradients added to slice by slice are left in the caches where all that the stage's
+  // layers add to between two slices is at most 64 MB.  Per-slice mode, 256-token slices,
+  // two sequences, kept against stored past the caches: width 1024, one layer (50 MB)
+  // 1227 against 1241 us, 768 (28 MB) 1107 / 1112; two layers of 1024 (100 MB) 2551 /
+  // 2539, one of 1536 (113 MB) 1346 / 1341, of 2048 (201 MB) 1778 / 1749.
+  const double grad_mb = S->cfg.n_layers * ((4.0 * A + 2.0 * F) * H) * 4e-6;
+  const int keep = !ow && S->cfg.wgrad_mode == TP_WGRAD_PER_SLICE && grad_mb <= 64;
   double flops = 0, bytes = 0;
   for (GemmArgs& gi : g) {
-    gi.overwrite = ow;
+    gi.overwrite = ow, gi.keep = keep;
     gi.ws = S->sc.splitk, gi.ws_elems = (long)S->sc.splitk_elems;
     flops += 2.0 * gi.M * gi.N * gi.K, bytes += gemm_bytes(gi, e);
   }

@@ -83,6 +83,9 @@ struct GemmArgs {
   // EPI_ACC_F32 only: store acc instead of adding it (the destination's old
   // contents are never read)
   int overwrite = 0;
+  // EPI_ACC_F32 in gemm_dw_group: the gradients are added to again soon and fit the
+  // caches (one value for the whole group)
+  int keep = 0;
   // LayerNorm to run on the output rows by a launcher that reduces split partial
   // sums; *norm_done tells whether it has (else the caller launches it)
   const RowNorm* norm = nullptr;
