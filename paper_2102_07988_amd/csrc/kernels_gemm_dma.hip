@@ -1,6 +1,7 @@
-// bf16 GEMM for k-aligned shapes: global -> LDS by the CDNA4 LDS DMA
-// (global_load_lds_dwordx4, 16 bytes per lane straight into LDS), a ring of
-// STAGES k-tiles in flight, and matrix-core reads straight from LDS:
+// bf16 (and fp16) GEMM of aligned operands, any number of rows, a last k-tile that need
+// not be whole: global -> LDS by the CDNA4 LDS DMA (global_load_lds_dwordx4, 16
+// bytes per lane straight into LDS), a ring of STAGES k-tiles in flight, and
+// matrix-core reads straight from LDS:
 //  - k-contiguous operand tiles ([row][64 k], 128-byte rows) are read with
 //    ds_read_b128 (8 consecutive k for one row);
 //  - operands contiguous along m/n stay in their global orientation in LDS
@@ -76,8 +77,8 @@ __device__ inline void dma16(const uint16_t* g, uint16_t* lds_wave_base) {
 
 // DMA of one R x BK operand tile into LDS.  KC: X(r, k) = X[r * ld + k];
 // MC: X(r, k) = X[k * ld + r].  Rows/columns past rmax are clamped to valid
-// memory (their products are never stored); k is always in range (the caller
-// guarantees whole k-tiles).  The per-lane part of every chunk address is a
+// memory (their products are never stored); issue takes whole k-tiles, issue_tail and
+// zero_tail a last one that is not.  The per-lane part of every chunk address is a
 // byte offset from the k-origin of the tile, computed once per output tile;
 // each k-tile only moves the wave-uniform origin (X + k for KC, X + k * ld for
 // MC), so the loads take the scalar-base + 32-bit vector-offset form.  The
@@ -774,7 +775,8 @@ hipError_t run_cfg(int cfg, const GemmArgs& a, hipStream_t s, int splits, int sp
     // Two wave groups over the reduction: a wave tile twice as large reads fewer
     // LDS bytes per product (64x128 tiles of eight waves: 48 instead of 64 KB a
     // k-tile), which with the DMA's writes bounds these tiles: 256 x 6144 x 2048 17.4 ->
-    // 15.8 us, 256 x 2048 x 2048 13.2 -> 11.7 us.
+    // 15.8 us, 256 x 2048 x 2048 13.2 -> 11.7 us (graph replays of one product; the first
+    // takes 19 us among a stage's other kernels).
     switch (cfg) {
       case T128x128:
         return run_dma<128, 128, 64, 2, 2, 2, A_KC, B_KC, 4, 4, F16, TAIL>(a, s, splits, 0, 0);
@@ -897,7 +899,8 @@ long reference_partials(const GemmArgs& a) {
 // What decides: a CU moves operands at 45-65 GB/s, more with two or three
 // workgroups on it, so narrow products want small tiles that use every CU without
 // partial sums (256 x 3072 x 1024: 14.5 -> 9 us, 256 x 8192 x 2048 with a GELU: 23 ->
-// 17.5 us), wide ones large tiles that move few bytes per flop.
+// 17.5 us, replays as in the sweep; 22 us among a stage's other kernels), wide ones large
+// tiles that move few bytes per flop.
 //   t = 3.6 + |(main + GELU, stream)| + epilogue bytes + (split: 2.1 + 0.16 per
 //   split + partials)
 // with stream = the weights (once from HBM, again from the caches for every further
@@ -912,8 +915,12 @@ TileChoice choose_tiles(const GemmArgs& a, bool tail) {
                                 {T256x256, 256, 256, 1, 3.427, 1.3320, 1.3828, 0.0}};
   const int nkt = cdiv(a.K, 64);
   const double wmb = (double)a.N * a.K * 2e-6, amb = (double)a.M * a.K * 2e-6;
-  // a weight matrix past the caches' share (with the line at 8e6 the 2048-wide stage
-  // took 4217 us for 4115)
+  // Weights that the caches no longer hold when their next slice comes.  What else a
+  // layer touches is not known here, so the line was placed by measuring stages on both
+  // sides of it (8e6 / 18e6 / 40e6, 256-token slices, one layer, us): 1536 wide 793 / 793
+  // / 793, 2048 1012 / 966 / 966, 2560 1329 / 1333 / 1332, 3072 1610 / 1616 / 1624, 4096
+  // 2255 / 2270 / 2268, 5120 3153 / 3165 / 3158; 64-token forward 3072 wide 734 / 733 /
+  // 770; two layers alike.
   const bool cold = (double)a.N * a.K >= 18e6;
   const long room = a.ws ? a.ws_elems : 0;
   const bool gelu = a.epi == EPI_GELU || a.epi == EPI_DGELU;

@@ -84,10 +84,10 @@ __device__ inline void st(T* p, float v) {
 // GELU, tanh form: 0.5 z (1 + tanh(y)), y = sqrt(2/pi) (z + 0.044715 z^3),
 // evaluated as z s with the sigmoid s = 1 / (1 + e^(-2y)) = (1 + tanh(y)) / 2: the
 // same function, one v_exp_f32 and one v_rcp_f32 in place of tanhf's branches, and
-// no 1 + tanh cancellation for negative z.  A 128 x 128 tile of four waves
-// evaluates 64 of these per lane with one wave per SIMD to hide behind, so the
-// tanhf form was about 5.6 us of each 36 us product of 256 x 8192 x 2048 with a
-// GELU or GELU' epilogue (2 layers of width 2048, 8 slices: 5482 -> 5303 us).
+// no 1 + tanh cancellation for negative z.  An epilogue evaluates 16-64 of these per
+// lane with few waves to hide behind: in the 128 x 128 tiles of four waves that the
+// product of 256 x 8192 x 2048 ran in when this was measured, the tanhf form was 5.6 of
+// its 36 us (2 layers of width 2048, 8 slices: 5482 -> 5303 us).
 __device__ inline float gelu_sigmoid(float z) {
   const float k = -2.3022081981f, a = 0.044715f;  // -2 log2(e) sqrt(2/pi)
   return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(k * (z + a * z * z * z)));
