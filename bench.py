@@ -9,8 +9,8 @@ second: per layer and slice, 24 n H^2 (projections) + 4 H per causal
 
 Prints one JSON line.  Per-kernel-class times are measured with HIP events on
 the stage's stream; `roofline` reports one kernel: the deferred dW GEMM (the
-largest single kernel) in the deferred mode, else the class with the largest
-total time.  `cpu_baseline` times the fp64 CPU oracle on a bounded sample of
+largest single kernel, one launch of a layer's four products) in the deferred
+mode, else the class with the largest total time.  `cpu_baseline` times the fp64 CPU oracle on a bounded sample of
 the same workload (one layer, a short slice).
 """
 from __future__ import annotations
@@ -51,7 +51,7 @@ PEAK_HBM_GBS = 8000.0
 TRAFFIC = {
     "gemm_bwd_dw_tn": {"workload": "gpt3-175b-stage", "grad_buffers": "overwrite",
                        "source": "paper_2102_07988_amd/csrc/kernels_gemm_dma.hip",
-                       "sha256_16": "63b4dc6c732fc8bf", "bytes_per_launch": 4555134686},
+                       "sha256_16": "ddf2cb654119da0d", "bytes_per_launch": 18157540732},
 }
 
 
@@ -482,9 +482,9 @@ def main():
                              "achieved_tflops": round(s["flops"] / secs / 1e12, 2),
                              "achieved_gbs": round(s["bytes"] / secs / 1e9, 1)}
         # the roofline names one kernel: with deferred weight gradients the
-        # largest single kernel is the dW GEMM (one launch per call); the slice
-        # GEMM classes are larger only in sum, each call being a split GEMM
-        # kernel plus its reduction
+        # largest single kernel is the dW GEMM (a launch computes the four products
+        # of a layer); the slice GEMM classes are larger only in sum, each call being
+        # a split GEMM kernel plus its reduction, which may carry a LayerNorm
         dom = max(stats, key=lambda k: stats[k]["total_ms"])
         if args.wgrad == "deferred" and "gemm_bwd_dw_tn" in stats:
             dom = "gemm_bwd_dw_tn"

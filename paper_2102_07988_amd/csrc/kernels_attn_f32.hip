@@ -19,8 +19,8 @@
 // into registers, and the waves' partial results meet in LDS in wave order at
 // the end (deterministic, no atomics).  Slices of 256 tokens after up to 768,
 // against one block per query row with a serial key loop and atomic dK/dV:
-// 16 heads of 64 in fp32, forward 130 -> 21 us, backward 1099 -> 82 us a launch;
-// 16 heads of 32 in bf16, forward 72 -> 16 us, backward 543 -> 46 us.
+// 16 heads of 64 in fp32, forward 130 -> 19 us, backward 1099 -> 70 us a slice;
+// 16 heads of 32 in bf16, forward 72 -> 13 us, backward 543 -> 45 us.
 #include "tp_common.hpp"
 #include "tp_kernels.hpp"
 

@@ -1074,7 +1074,7 @@ bool dw_covered(const GemmArgs& a) {
 // The weight-gradient products of a layer (count <= 4, one reduction length) in one
 // launch, where that is modelled faster than one launch each with its own tiles and
 // splits: narrow gradients fill the chip together (1024 wide, 256 tokens a slice: 36 ->
-// 28 us, 5 TB/s of gradient read and written), wide ones share their part-empty last
+// 27 us, 3.7 TB/s of gradient read and written), wide ones share their part-empty last
 // rounds (2048 wide, 2048 tokens: 238 -> 202 us; 8-way shard of 12288: 1038 -> 963 us).
 // hipErrorNotSupported: not covered, or separate launches are better.
 hipError_t gemm_dw_group(const GemmArgs* g, int count, hipStream_t s) {

@@ -19,7 +19,7 @@
 // reduction when they are still few, products of many tiles 128 x 128.
 // Width 1024, 256-token slices, averages over a layer's products against the
 // strided FMA kernel: forward 337 -> 23 us (+ 5 us reduction), dX 468 -> 22 us (+ 5),
-// weight gradients over 1024 tokens 253 -> 72 us.  About 60 % of the fp32 matrix rate;
+// weight gradients over 1024 tokens 253 -> 69 us: 71, 74 and 94 TFLOP/s of 157 nominal;
 // reading the fragments a step ahead, or one workgroup a CU without splits, was 2-4 %
 // slower over the layer.
 #include "tp_common.hpp"

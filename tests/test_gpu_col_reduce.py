@@ -1,5 +1,5 @@
 """Bias and LayerNorm-parameter gradients (the column sums of a layer, one launch):
-row counts at the edges of a row chunk (256) and column counts off the 64-column
+row counts around the least rows of a chunk (256) and of two (512) and column counts off the 64-column
 blocks, stored and added, against the oracle.
 
 Tolerances: fp32 3e-5 (unit roundoff 6e-8, root of 4096 terms, 8 chained products),
@@ -13,8 +13,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype,H,heads,L", [
-    ("bf16", 512, 4, 255), ("bf16", 512, 4, 257), ("bf16", 48, 3, 600), ("fp32", 80, 5, 257),
-    ("fp32", 256, 4, 1),
+    ("bf16", 512, 4, 255), ("bf16", 512, 4, 257), ("bf16", 512, 4, 511), ("bf16", 512, 4, 513),
+    ("bf16", 48, 3, 600), ("fp32", 80, 5, 257), ("fp32", 256, 4, 1),
 ])
 @pytest.mark.parametrize("wgrad", ["deferred", "per_slice"])
 def test_stored_then_added(dtype, H, heads, L, wgrad):
